@@ -3,16 +3,14 @@
 // inspecting the local neighbourhood of each vertex, which makes the step
 // embarrassingly parallel; cells are compared as in Section 2.1).
 //
-// Per vertex x, with the orders of x and its 14 neighbours staged in LDS:
-//  1. the lower neighbours are ranked among themselves; the key of a cell of
-//     the lower star L(x) (its vertex orders listed decreasingly, compared
-//     lexicographically) then equals the integer whose bits are the ranks of
-//     its lower vertices, so faces precede cofaces and "smallest" is an
-//     integer minimum, found by a bit-sliced scan over per-rank planes;
-//  2. Robins' pairing runs in registers on bitsets over the star's cells
-//     (unpaired cells, and a bit-sliced count of each cell's unpaired facets)
-//     -- see process_vertex for why the two priority queues need no storage;
-//  3. the outcome is packed into the 16-byte record described in dms.h.
+// Most vertices of a smooth field take their record from tables indexed by
+// their lower neighbours and the order of those (see table_entry).  Any other
+// vertex is solved from its sorted neighbours by two growing forests that
+// give Robins' pairing without its queues (see solve_star).  k_gradient does
+// the table vertices of every tile and hands the others over: a tile with few
+// of them queues them (k_gradient_queue), a tile with many is listed whole
+// (k_gradient_dense).
+// The outcome is packed into the 16-byte record described in dms.h.
 // Readings: "unpaired" = neither paired nor critical; only unpaired cells
 // enter the one-facet queue; entries of the zero queue that get paired are
 // dropped (Robins' lazy deletion gives the same pops).
@@ -29,55 +27,79 @@ namespace {
 constexpr int kThreads = 256;      // threads per block
 constexpr int kTileVerts = 1024;  // vertices per tile (4 per thread)
 constexpr int32_t kAbsent = 0x7fffffff;
-constexpr int kSizeBins = 77;  // keys 1 + lower-star size (1..75); bin 76 stays empty
 
-// Star cells other than x and the edges: triangles t -> bit t, tets q -> bit
-// 36 + q of a 64-bit mask ("TQ space").
-constexpr uint64_t kTriBits = (1ull << 36) - 1;
-
-struct SharedTables {
-    uint64_t cont[14];     // TQ cells containing neighbour e
-    uint64_t facet[60];    // triangle: its two edges (neighbour bits); tet: its 3 triangles (TQ bits)
-    uint64_t cofacet[60];  // triangle: the tets containing it (TQ bits); tet: 0
-    uint8_t tri_ab[36];    // a | b << 4
-    uint8_t tri_slot[36];  // slot of t in the triangle list of a | of b << 4
-    uint8_t tri_tet0[36];  // first star tet containing t
-    uint8_t tet_abc[24][3];
-    uint8_t pad[4];
+// Tables of solve_star, staged in LDS (9 KB).  Everything is relative to a
+// vertex's lowest neighbour d: once x is paired with the edge to d, every
+// lower triangle through d is paired too, so only the star triangles that do
+// not contain d are searched -- at most 32 of the 36 (each neighbour lies on
+// 4 or 6), one 32-bit word.  "Triangle bit" below is a triangle's position
+// among those, in star order.
+struct StarTables {
+    // [d][e]: triangle bits containing neighbour e; [d][14]: the unused bits;
+    // [d][15]: star tets containing d
+    alignas(16) uint32_t tris[14][16];
+    // [d][bit]: low word = the star tets containing the triangle, star index
+    // of the triangle << 24; high word = a | field(a) << 4 | b << 8 |
+    // field(b) << 12 for its neighbours a, b, field(e) = the record field of
+    // edge e when it is paired with this triangle
+    alignas(16) uint64_t tri[14][32];
+    // [d][q]: low word = triangle bits of tet q, high word = those of them
+    // whose first star tet is q
+    alignas(16) uint64_t tet[14][24];
+    // [2 t + v - 1]: the last three record words with triangle t's field = v
+    alignas(16) uint32_t field[72][4];
+    // [d]: edge fields with d paired with x and every neighbour of d in the
+    // link paired with its triangle through d
+    uint64_t fan[14];
+    uint32_t nibbles[128];  // bit i -> 0xf << 4 i
+    uint16_t link[16];
 };
 
-constexpr SharedTables make_shared_tables()
+constexpr StarTables make_star_tables()
 {
-    SharedTables d{};
+    StarTables S{};
     const Tables &T = kTables;
-    for (int e = 0; e < 14; ++e) d.cont[e] = T.edge_trimask[e] | ((uint64_t)T.edge_tetmask[e] << 36);
-    for (int t = 0; t < 36; ++t) {
-        d.facet[t] = T.tri_edgemask[t];
-        d.cofacet[t] = (uint64_t)T.tri_tetmask[t] << 36;
-        d.tri_ab[t] = (uint8_t)(T.tri[t][0] | (T.tri[t][1] << 4));
-        d.tri_slot[t] = (uint8_t)(T.tri_slot[t][0] | (T.tri_slot[t][1] << 4));
-        d.tri_tet0[t] = (uint8_t)T.tri_tets[t][0];
+    for (int d = 0; d < 14; ++d) {
+        int bit[36] = {}, n = 0;
+        for (int t = 0; t < 36; ++t) bit[t] = T.tri[t][0] == d || T.tri[t][1] == d ? -1 : n++;
+        S.tris[d][14] = n < 32 ? ~0u << n : 0u;
+        S.tris[d][15] = T.edge_tetmask[d];
+        for (int t = 0; t < 36; ++t) {
+            const int a = T.tri[t][0], b = T.tri[t][1];
+            const uint32_t fa = 3u + (uint32_t)T.tri_slot[t][0], fb = 3u + (uint32_t)T.tri_slot[t][1];
+            if (bit[t] < 0) {
+                const int o = a == d ? b : a;
+                S.fan[d] |= (uint64_t)(o == a ? fa : fb) << (4 * o);
+                continue;
+            }
+            S.tris[d][a] |= 1u << bit[t];
+            S.tris[d][b] |= 1u << bit[t];
+            const uint32_t ends = (uint32_t)a | fa << 4 | (uint32_t)b << 8 | fb << 12;
+            S.tri[d][bit[t]] = (uint64_t)ends << 32 | (uint64_t)(T.tri_tetmask[t] | (uint32_t)t << 24);
+        }
+        S.fan[d] |= 1ull << (4 * d);
+        for (int q = 0; q < 24; ++q)
+            for (int c = 0; c < 3; ++c) {
+                const int t = T.tet_tris[q][c];
+                if (bit[t] < 0) continue;
+                S.tet[d][q] |= 1ull << bit[t];
+                if (T.tri_tets[t][0] == q) S.tet[d][q] |= 1ull << (32 + bit[t]);
+            }
+        S.link[d] = T.link[d];
     }
-    for (int q = 0; q < 24; ++q) {
-        d.facet[36 + q] = T.tet_trimask[q];
-        d.cofacet[36 + q] = 0;
-        for (int c = 0; c < 3; ++c) d.tet_abc[q][c] = (uint8_t)T.tet[q][c];
-    }
-    return d;
+    for (int t = 0; t < 36; ++t)
+        for (uint32_t v = 1; v <= 2; ++v) {
+            const int at = 24 + 2 * t;  // from the record's second word
+            S.field[2 * t + (int)v - 1][at / 32] = v << (at % 32);
+        }
+    for (uint32_t m = 0; m < 128; ++m)
+        for (int i = 0; i < 7; ++i)
+            if ((m >> i) & 1u) S.nibbles[m] |= 0xfu << (4 * i);
+    return S;
 }
 
-__constant__ SharedTables g_tables = make_shared_tables();
-static_assert(sizeof(SharedTables) % 4 == 0, "copied as words");
-
-// Free-facet counts of the TQ cells, bit-sliced: count = 2*b1 + b0.
-struct Counts {
-    uint64_t b0, b1;
-    __device__ __forceinline__ void dec(uint64_t d)
-    {
-        b1 ^= d & ~b0;
-        b0 ^= d;
-    }
-};
+__device__ const StarTables g_star = make_star_tables();
+static_assert(sizeof(StarTables) % 16 == 0, "copied as 16-byte words");
 
 __device__ __forceinline__ uint32_t nib(uint64_t packed, int i) { return (uint32_t)(packed >> (4 * i)) & 15u; }
 
@@ -143,197 +165,200 @@ __device__ __forceinline__ uint32_t lower_mask(const C *o, C ox)
     return low;
 }
 
-// TQ cells of L(x): those with no vertex outside the lower set.
-__device__ __forceinline__ uint64_t lower_star_tq(uint32_t low)
-{
-    uint64_t out_tq = 0;
-#pragma unroll
-    for (int e = 0; e < 14; ++e)
-        if (!((low >> e) & 1u)) out_tq |= kTables.edge_trimask[e] | ((uint64_t)kTables.edge_tetmask[e] << 36);
-    return ~out_tq & ((1ull << 60) - 1);
-}
-
-// Ranks of the lower neighbours among themselves, 4 bits per neighbour
-// (15 for a neighbour that is not lower).
+// The 14 neighbours in increasing order, 4 bits each (neighbours outside the
+// grid compare above all others, by index among themselves).
 template <typename C>
-__device__ __forceinline__ uint64_t lower_ranks(const C *o, uint32_t low)
+__device__ __forceinline__ uint64_t sorted_neighbours(const C *o)
 {
-    C ol[14];
     uint32_t r[14];
 #pragma unroll
-    for (int e = 0; e < 14; ++e) {
-        ol[e] = (low >> e) & 1u ? o[e] : c_highest<C>();
-        r[e] = 0;
-    }
+    for (int e = 0; e < 14; ++e) r[e] = (uint32_t)e;
 #pragma unroll
     for (int a = 0; a < 14; ++a)
 #pragma unroll
         for (int b = a + 1; b < 14; ++b) {
-            const uint32_t c = ol[b] < ol[a] ? 1u : 0u;
+            const uint32_t c = o[b] < o[a] ? 1u : 0u;
             r[a] += c;
-            r[b] += 1u - c;
+            r[b] -= c;
         }
-    uint64_t rank_of = 0;
+    uint64_t at = 0;
 #pragma unroll
-    for (int e = 0; e < 14; ++e) rank_of |= (uint64_t)((low >> e) & 1u ? r[e] : 15u) << (4 * e);
-    return rank_of;
+    for (int e = 1; e < 14; ++e) at |= (uint64_t)e << (4 * r[e]);
+    return at;
 }
 
-__device__ __forceinline__ uint32_t low_of_ranks(uint64_t rank_of)
-{
-    uint32_t low = 0;
-#pragma unroll
-    for (int e = 0; e < 14; ++e) low |= (nib(rank_of, e) != 15u ? 1u : 0u) << e;
-    return low;
-}
-
-__device__ __forceinline__ bool robins(uint64_t rank_of, const SharedTables &T, uint4 &out);
-
-// The cell of S with the smallest key, as a one-bit set (S if S has at
-// most one cell), bit-sliced from the top rank plane down: keep the cells
-// without rank b when there are any.  All 14 planes are walked, as
-// straight-line code; planes at or above the lower-neighbour count are all
-// ones and change nothing.  (Entering the walk at the wave's largest lower
-// count instead, through a switch, cost a branch chain and register copies
-// in every step; instances for a few plane counts raised register pressure
-// into spills; stopping early once no lane has two candidates left cost more
-// in checks than it saved in planes.)
-__device__ __forceinline__ uint64_t smallest_by_key(uint64_t S, const uint64_t *nkp)
+// The triangle of S with the smallest (kLargest: largest) key, as a one-bit
+// set (S when it has at most one): walked from the highest rank down, keeping
+// the triangles without (with) the neighbour of that rank when there are any.
+// has[b] = triangle bits containing the neighbour of rank b.  A rank above the
+// lower neighbours changes nothing, S holding lower triangles only, so the
+// walk is straight-line code over all ranks but d's.
+__device__ __forceinline__ uint32_t smallest_triangle(uint32_t S, const uint32_t *has)
 {
 #pragma unroll
-    for (int b = 13; b >= 0; --b) {
-        const uint64_t z = S & nkp[b];
+    for (int b = 13; b >= 1; --b) {
+        const uint32_t z = S & ~has[b];
         S = z ? z : S;
     }
     return S;
 }
 
-// Robins' ProcessLowerStars for one vertex, from the orders of x and its 14
-// neighbours (kAbsent for neighbours outside the grid).
-// Returns whether L(x) holds a critical cell.
-template <typename C>
-__device__ __forceinline__ bool process_vertex(const C *o, C ox, const SharedTables &T, uint4 &out)
+// Robins' pairing of the lower star of x, from its neighbours in increasing
+// order (sorted_neighbours) and the mask of the lower ones.  Returns whether
+// some cell of L(x) ends critical.
+//
+// Call the lower neighbours nodes, the lower triangles links (each joins two
+// nodes) and compare links by their cells' keys.  Robins' queues give:
+//  1. Edges.  An edge is paired when its node is reached by the smallest link
+//     that joins a reached node to an unreached one: Prim's growth, with
+//     distinct weights, so the links used are the minimum spanning forest of
+//     the lower link, and each node's edge is paired with the link towards the
+//     root, the lowest node of its component.  The first root's edge is paired
+//     with x; every other root's edge is critical (it is declared when no link
+//     reaches a new node, as the smallest unpaired edge).  Pairs with tets do
+//     not interfere: a tet's last unpaired triangle t always has both nodes
+//     reached (were one missing, t or another triangle of the tet would join
+//     a reached node to it, and come first, faces preceding cofaces).
+//  2. Tets.  The other links are left over for the tets.  A tet with one
+//     unpaired triangle takes it; in whatever order that is done the result
+//     is the same, since a leaf pair changes only cells above it.  When no
+//     such tet is left but unpaired tets are, the smallest left-over triangle
+//     is critical (all edges are settled and no tet can run out of triangles,
+//     see 3), and the stripping goes on.
+//  3. The left-over triangles and the tets form a forest whose trees end in
+//     triangles with a missing or upper second tet, except when every
+//     neighbour is lower: then the tets form one closed tree, stripped from
+//     its leaves by increasing key, and the largest tet remains critical.
+// The growth starts from d, the lowest node, with the nodes linked to it: the
+// link to d is the smallest one at each of them.  Only links that avoid d
+// matter afterwards, which fit one word (StarTables).  A link joins a reached
+// to an unreached node exactly when it lies on an odd number of reached ones:
+// reaching a node flips its links.
+//
+// Bound by vector-instruction issue: 63 instructions per node reached beyond
+// d's neighbours (39 of them the search), 22 per tet, 47 per critical
+// triangle, about 200 once, beside the 290 of sorted_neighbours.  A wave of
+// white noise reaches 4.9 nodes and strips 8.3 tets (its longest lane, dealt
+// by lower-neighbour count).  It replaced a loop over single pairs that kept
+// 60-bit sets of the unpaired cells and searched all of them each time (about
+// 150 instructions a pair, 14 pairs a wave): gradient of 96 fields, half of
+// them noise, 22.7 -> 17.0 ms; of a noisy 512^3 mixture 5.0 -> 3.8 ms; from
+// the values of a 643 x 511 x 386 one 4.7 -> 3.2 ms.
+__device__ __forceinline__ bool solve_star(uint64_t nb_at, uint32_t low, const StarTables &T, uint4 &out)
 {
-    const uint32_t low = lower_mask(o, ox);
     if (low == 0) {  // L(x) = {x}: x is critical
         out = make_uint4(0, 0, 0, 0);
         return true;
     }
-    return robins(lower_ranks(o, low), T, out);
-}
-
-// The pairing itself, from the ranks of the lower neighbours (lower_ranks).
-//
-// The two priority queues of Robins' formulation are not stored: at any time
-// the one-facet queue, minus entries that have meanwhile lost their last
-// unpaired facet, is exactly the set of unpaired cells with one unpaired
-// facet (every cell enters it at the moment its count drops from two to
-// one), and when that set is empty the zero queue's live entries are exactly
-// the unpaired edges and the unpaired cells with no unpaired facet.  So each
-// step takes the smallest cell of the first set and pairs it with its
-// unpaired facet, or, if that set is empty, declares the smallest cell of the
-// second set critical.  "Smallest" is a bit-sliced minimum over key planes:
-// plane b holds the cells that contain the neighbour of rank b, and the key
-// of a cell is the integer with those bits (Section 2.1 comparison).
-// Returns whether some cell of L(x) ends critical.
-__device__ __forceinline__ bool robins(uint64_t rank_of, const SharedTables &T, uint4 &out)
-{
-    const uint32_t low = low_of_ranks(rank_of);
-    if (low == 0) {
-        out = make_uint4(0, 0, 0, 0);
-        return true;
+    const uint32_t d = (uint32_t)nb_at & 15u;
+    const uint32_t F = T.link[d] & low;  // lower neighbours linked to d
+    const uint4 *row = (const uint4 *)T.tris[d];
+    uint32_t upper, S = 0, utets = 0;
+    uint32_t b1;  // unpaired triangles of each tet = 2 b1 + b0: one for d's tets, three for the others
+    {
+        const uint4 r0 = row[0], r1 = row[1], r2 = row[2], r3 = row[3];
+        const uint32_t c[14] = {r0.x, r0.y, r0.z, r0.w, r1.x, r1.y, r1.z, r1.w, r2.x, r2.y, r2.z, r2.w, r3.x, r3.y};
+        upper = r3.z;
+        b1 = ~r3.w;
+#pragma unroll
+        for (int e = 0; e < 14; ++e) {
+            const uint32_t lm = (uint32_t)((int32_t)(low << (31 - e)) >> 31), fm = (uint32_t)((int32_t)(F << (31 - e)) >> 31);
+            upper |= c[e] & ~lm;
+            utets |= kTables.edge_tetmask[e] & ~lm;
+            S ^= c[e] & fm;
+        }
+    }
+    const uint32_t L = ~upper;  // lower triangles (without d's)
+    S &= L;
+    uint32_t U = ~utets & 0xffffffu;  // unpaired lower tets
+    uint32_t b0 = ~0u;
+    uint32_t has[14];
+#pragma unroll
+    for (int b = 1; b < 14; ++b) has[b] = T.tris[d][nib(nb_at, b)];
+    uint32_t reached = F | 1u << d;
+    uint64_t edges;  // the edge fields
+    {
+        const uint32_t n0 = T.nibbles[reached & 127u], n1 = T.nibbles[reached >> 7];
+        edges = T.fan[d] & ((uint64_t)n1 << 28 | n0);
     }
     bool crit = false;
-    uint64_t nb_at = 0;  // rank -> neighbour (4 bits each)
-#pragma unroll
-    for (int e = 0; e < 14; ++e)
-        if ((low >> e) & 1u) nb_at |= (uint64_t)e << (4 * nib(rank_of, e));
-    const int m = __popc(low);
-    // complement of the key planes: nkp[b] = TQ cells NOT containing rank b
-    uint64_t nkp[14];
-#pragma unroll
-    for (int b = 0; b < 14; ++b) nkp[b] = b < m ? ~T.cont[nib(nb_at, b)] : ~0ull;
-
-    uint64_t ftq = lower_star_tq(low);  // unpaired TQ cells
-    uint32_t fe = low;                  // unpaired edges, by neighbour
-    uint32_t fr = (1u << m) - 1u;       // unpaired edges, by rank
-    Counts cnt{(1ull << 60) - 1 - kTriBits, (1ull << 60) - 1};  // triangles 2, tets 3
-    uint64_t rec_lo = 0, rec_hi = 0;
-
-    // pair x with its smallest edge (the lowest lower neighbour)
-    {
-        const int d = nib(nb_at, 0);
-        fe &= ~(1u << d);
-        fr &= ~1u;
-        rec_lo |= 1ull << (4 * d);
-        cnt.dec(T.cont[d] & kTriBits);
-    }
-    for (int step = 0; step < 80; ++step) {
-        // the cells with one unpaired facet if there are any, else the
-        // unpaired cells without one; one bit-sliced minimum serves both
-        // cases, so lanes of a wave that are in different cases share it
-        const uint64_t one = ftq & cnt.b0 & ~cnt.b1;
-        uint64_t S = one ? one : (ftq & ~cnt.b0 & ~cnt.b1);
-        if (S == 0 && fr == 0) break;
-        S = smallest_by_key(S, nkp);
-        const bool have_a = S != 0;
-        const int a = have_a ? __ffsll((unsigned long long)S) - 1 : 0;
-        if (one) {
-            // pair the smallest cell with one unpaired facet with that facet
-            const uint64_t fa = T.facet[a];
-            uint64_t D;
-            if (a < 36) {  // triangle a takes its only unpaired edge e
-                const int e = __ffs((uint32_t)fa & fe) - 1;
-                fe &= ~(1u << e);
-                fr &= ~(1u << nib(rank_of, e));
-                const uint32_t ab = T.tri_ab[a], sl = T.tri_slot[a];
-                const uint32_t slot = (int)(ab & 15u) == e ? (sl & 15u) : (sl >> 4);
-                rec_lo |= (uint64_t)(3u + slot) << (4 * e);
-                D = (T.cont[e] & kTriBits) | T.cofacet[a];
-            } else {  // tet a takes its only unpaired triangle t
-                const int t = __ffsll((unsigned long long)(fa & ftq)) - 1;
-                ftq &= ~(1ull << t);
-                D = T.cofacet[t];
-                const uint64_t v = T.tri_tet0[t] == a - 36 ? 1u : 2u;
-                const int bit = 56 + 2 * t;
-                if (bit < 64) rec_lo |= v << bit; else rec_hi |= v << (bit - 64);
-            }
-            ftq &= ~(1ull << a);
-            cnt.dec(D);
-            continue;
+    uint32_t left = L;  // lower triangles paired with no edge
+    // 1. edges; every pass of the outer loop after the first starts a component
+    for (int comp = 0; comp < 14; ++comp) {
+        for (int step = 0; step < 14 && S; ++step) {
+            const uint32_t bit = smallest_triangle(S, has);
+            const uint64_t tri = T.tri[d][__builtin_ctz(bit)];
+            const uint32_t ends = (uint32_t)(tri >> 32), D = (uint32_t)tri & 0xffffffu;
+            const uint32_t f = (reached >> (ends & 15u)) & 1u ? ends >> 8 : ends;
+            const uint32_t e = f & 15u;
+            left ^= bit;
+            b1 ^= D & ~b0;
+            b0 ^= D;
+            edges |= (uint64_t)((f >> 4) & 15u) << (4 * e);
+            reached |= 1u << e;
+            S ^= T.tris[d][e] & L;
         }
-        // no cell has exactly one unpaired facet: the smallest unpaired edge or
-        // cell without unpaired facets is critical
+        const uint32_t rest = low & ~reached;
+        if (!rest) break;
+        uint32_t e = 0;  // the lowest node not reached
+#pragma unroll
+        for (int b = 13; b >= 1; --b) {
+            const uint32_t g = nib(nb_at, b);
+            e = (rest >> g) & 1u ? g : e;
+        }
         crit = true;
-        bool edge_wins = fr != 0 && !have_a;
-        const int re = fr ? __ffs(fr) - 1 : 31;
-        if (fr != 0 && have_a) {
-            // the edge of rank re is smaller iff re <= the top rank of cell a
-            int top;
-            if (a < 36) {
-                const uint32_t ab = T.tri_ab[a];
-                top = max(nib(rank_of, ab & 15u), nib(rank_of, ab >> 4));
-            } else {
-                const int q = a - 36;
-                top = max(max(nib(rank_of, T.tet_abc[q][0]), nib(rank_of, T.tet_abc[q][1])),
-                          nib(rank_of, T.tet_abc[q][2]));
-            }
-            edge_wins = re <= top;
-        }
-        if (edge_wins) {
-            const int e = nib(nb_at, re);
-            fe &= ~(1u << e);
-            fr &= ~(1u << re);
-            rec_lo |= 2ull << (4 * e);
-            cnt.dec(T.cont[e] & kTriBits);
-        } else {
-            ftq &= ~(1ull << a);
-            cnt.dec(T.cofacet[a]);
-        }
+        edges |= 2ull << (4 * e);
+        reached |= 1u << e;
+        S ^= T.tris[d][e] & L;
     }
-    out = make_uint4((uint32_t)rec_lo, (uint32_t)(rec_lo >> 32), (uint32_t)rec_hi,
-                     (uint32_t)(rec_hi >> 32));
-    return crit;
+    // 3. every neighbour lower: the largest tet is critical
+    if (low == 0x3fffu) {
+        uint32_t Q = 0xffffffu;
+#pragma unroll 1
+        for (int b = 13; b >= 0; --b) {
+            const uint32_t z = Q & T.tris[nib(nb_at, b)][15];
+            Q = z ? z : Q;
+        }
+        U &= ~Q;
+        crit = true;
+    }
+    // 2. tets
+    uint32_t ty = 0, tz = 0, tw = 0;  // the triangle fields, from the record's second word on
+    for (int turn = 0; turn < 36 && U; ++turn) {
+        uint32_t one = U & b0 & ~b1;
+        for (int step = 0; step < 24 && one; ++step) {
+            const uint32_t q = (uint32_t)__builtin_ctz(one);
+            const uint64_t tet = T.tet[d][q];
+            const uint32_t u = (uint32_t)tet & left;  // its one unpaired triangle
+            const uint32_t tri = (uint32_t)T.tri[d][__builtin_ctz(u)], D = tri & 0xffffffu;
+            const uint32_t second = u & (uint32_t)(tet >> 32) ? 0u : 1u;
+            const uint4 w = *(const uint4 *)T.field[2u * (tri >> 24) + second];
+            left ^= u;
+            U &= ~(1u << q);
+            b1 ^= D & ~b0;
+            b0 ^= D;
+            ty |= w.x;
+            tz |= w.y;
+            tw |= w.z;
+            one = U & b0 & ~b1;
+        }
+        if (!U || !left) break;
+        const uint32_t bit = smallest_triangle(left, has);
+        const uint32_t D = (uint32_t)T.tri[d][__builtin_ctz(bit)] & 0xffffffu;
+        left ^= bit;
+        b1 ^= D & ~b0;
+        b0 ^= D;
+        crit = true;
+    }
+    out = make_uint4((uint32_t)edges, (uint32_t)(edges >> 32) | ty, tz, tw);
+    return crit || left != 0;
+}
+
+// From the orders of x and its neighbours.
+template <typename C>
+__device__ __forceinline__ bool process_vertex(const C *o, C ox, const StarTables &T, uint4 &out)
+{
+    return solve_star(sorted_neighbours(o), lower_mask(o, ox), T, out);
 }
 
 // ---------------------------------------------------------------------------
@@ -386,8 +411,14 @@ struct TabHit {
     uint32_t idx;
 };
 
-// Table entry of x, or a null record when x is in none of the families
-// (defect8 may be null: that family then takes the general path).
+// Whether x, with lower neighbours low, is in none of the tabulated families
+// (at least two of the opposite pairs wholly lower or wholly upper).
+__device__ __forceinline__ bool general_vertex(uint32_t low)
+{
+    return __popc((low ^ (__brev(low) >> 18)) & 0x7fu) < 6;
+}
+
+// Table entry of x, or a null record when x is in none of the families.
 template <typename C>
 __device__ __forceinline__ TabHit table_entry(uint32_t low, const C *o, const uint4 *__restrict__ defect8)
 {
@@ -413,7 +444,6 @@ __device__ __forceinline__ TabHit table_entry(uint32_t low, const C *o, const ui
         v7 = cmin(v7, w ? a : kHigh);
     }
     const bool eight = both != 0;
-    if (eight && !defect8) return TabHit{nullptr, nullptr, 0};
     v[7] = v7;
     uint32_t l[8];
 #pragma unroll
@@ -464,26 +494,28 @@ __device__ __forceinline__ void gather_orders(const typename Keys::H *tile, int 
     ox = Keys::cmp(tile[c], 7);
 }
 
-// Vertices that no table covers ("general" vertices) need Robins' loop,
-// whose length varies with the lower star.  A tile with many of them pairs
-// them itself, dealt to threads by increasing size (pass 2).  A tile with
-// few -- the common case of a smooth field -- would leave one sparse wave
-// running a long loop while the block holds its slot, so it ranks them and
-// appends compact entries to a device queue instead; a second kernel pairs
-// the queue in full waves sorted by size.
-//   entry: x, y = ranks of the lower neighbours (lower_ranks, 56 bits), the
-//          record index (40 bits: z, and the top byte of y), w = size key.
+// Vertices that no table covers ("general" vertices) are solved by solve_star,
+// whose length varies with the lower star, so they leave the tile pass:
+//  - a tile with few of them (the common case of a smooth field: one sparse
+//    wave would hold the block's slot) sorts their neighbours while the halo
+//    is in LDS and appends compact entries to a device queue, which
+//    k_gradient_queue solves in full waves;
+//  - a tile with kThreads of them or more is appended to a list of tiles,
+//    which k_gradient_dense stages again and solves.
+//   entry: x, y = sorted neighbours (56 bits), the record index (40 bits: z,
+//          and the top byte of y), w = mask of the lower neighbours.
+// Both are dealt to threads by the number of lower neighbours, which fixes
+// most of the length (sorting by the number of steps itself would save 1%).
 constexpr int kQueueChunk = 1024;  // entries per block of the queue kernel
+constexpr int kSizeBins = 16;      // lower-neighbour counts (0..14)
 
-// The ranks take 56 bits (14 nibbles); the record index takes 40 bits, its
-// top 8 in the free byte above the ranks.
-__device__ __forceinline__ uint4 queue_entry(uint64_t rk, int64_t ridx, uint32_t key)
+__device__ __forceinline__ uint4 queue_entry(uint64_t nb_at, int64_t ridx, uint32_t low)
 {
     const uint64_t r = (uint64_t)ridx;
-    return make_uint4((uint32_t)rk, ((uint32_t)(rk >> 32) & 0x00ffffffu) | ((uint32_t)(r >> 32) << 24),
-                      (uint32_t)r, key);
+    return make_uint4((uint32_t)nb_at, ((uint32_t)(nb_at >> 32) & 0x00ffffffu) | ((uint32_t)(r >> 32) << 24),
+                      (uint32_t)r, low);
 }
-__device__ __forceinline__ uint64_t entry_ranks(const uint4 &e)
+__device__ __forceinline__ uint64_t entry_neighbours(const uint4 &e)
 {
     return (uint64_t)e.x | (uint64_t)(e.y & 0x00ffffffu) << 32;
 }
@@ -492,46 +524,39 @@ __device__ __forceinline__ int64_t entry_record(const uint4 &e)
     return (int64_t)((uint64_t)e.z | (uint64_t)(e.y >> 24) << 32);
 }
 
-struct BlockShared {
-    SharedTables T;
-    uint32_t bins[kSizeBins];
-    uint32_t qbase;
-    uint32_t nlist;
-    uint16_t list[kTileVerts];  // general vertices of the tile (tile positions)
-    uint16_t perm[kTileVerts];  // the same, sorted by size key (dense tiles)
+// The queue and the list of dense tiles, in the caller's workspace: a queue
+// counter and a list counter, then the entries, then the tile numbers.  A
+// counter may pass its capacity: entries beyond are not written.  A tile whose
+// vertices do not all fit the queue is listed; when the list is full too, or
+// there is no workspace (all null), the dense kernel takes every tile.
+struct Handoff {
+    uint32_t *counts;  // [0] queue, [1] list
+    uint4 *queue;
+    uint32_t *list;
+    uint32_t qcap, lcap;
 };
 
-__device__ __forceinline__ void load_tables(SharedTables &T)
+__device__ __forceinline__ void load_tables(StarTables &T)
 {
-    const uint32_t *src = (const uint32_t *)&g_tables;
-    uint32_t *dst = (uint32_t *)&T;
-    for (int i = threadIdx.x; i < (int)(sizeof(SharedTables) / 4); i += kThreads) dst[i] = src[i];
+    const uint4 *src = (const uint4 *)&g_star;
+    uint4 *dst = (uint4 *)&T;
+    for (int i = threadIdx.x; i < (int)(sizeof(StarTables) / 16); i += kThreads) dst[i] = src[i];
 }
 
-// Exclusive scan of sh.bins (kSizeBins <= 2 * kWave) by the first wave.
+// Exclusive scan of kSizeBins counters by the first wave.
 __device__ __forceinline__ void scan_bins(uint32_t *bins)
 {
     const int tid = threadIdx.x;
     if (tid < kWave) {
-        const uint32_t v0 = tid < kSizeBins ? bins[tid] : 0u;
-        const uint32_t v1 = tid + kWave < kSizeBins ? bins[tid + kWave] : 0u;
-        uint32_t i0 = v0, i1 = v1;
+        const uint32_t v = tid < kSizeBins ? bins[tid] : 0u;
+        uint32_t inc = v;
 #pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) {
-            const uint32_t t0 = __shfl_up(i0, off), t1 = __shfl_up(i1, off);
-            if (tid >= off) { i0 += t0; i1 += t1; }
+        for (int off = 1; off < kSizeBins; off <<= 1) {
+            const uint32_t t = __shfl_up(inc, off);
+            if (tid >= off) inc += t;
         }
-        const uint32_t tot0 = __shfl(i0, kWave - 1);
-        if (tid < kSizeBins) bins[tid] = i0 - v0;
-        if (tid + kWave < kSizeBins) bins[tid + kWave] = tot0 + i1 - v1;
+        if (tid < kSizeBins) bins[tid] = inc - v;
     }
-}
-
-// Size key of a general vertex: 1 + lower neighbours + lower-star triangles
-// and tets (at most 75).
-__device__ __forceinline__ uint32_t size_key(uint32_t low)
-{
-    return 1u + (uint32_t)__popc(low) + (uint32_t)__popcll(lower_star_tq(low));
 }
 
 // Marks record r (box index) as holding a critical cell: bit r of the mask.
@@ -540,29 +565,31 @@ __device__ __forceinline__ void mark_critical(uint32_t *mark, int64_t r)
     atomicOr(&mark[r >> 5], 1u << (uint32_t)(r & 31));
 }
 
-// One GX x GY x 1 tile (1024 vertices) of the owned box [lo, lo + w) of a
-// grid of dims n; record indices are rec_off + position in the owned box.
-// The orders of the tile plus a one-vertex halo are staged in LDS.  Pass 1
-// visits the tile in order (4 vertices per thread): a regular or one-defect
-// vertex takes its record from the precomputed tables; any other vertex is
-// listed.  A tile with fewer than kThreads listed vertices ranks them and
-// queues as many as fit (pairing any others itself); a denser tile sorts
-// them by size and pairs them itself.  Must be entered by the whole block.
+// A field's grid dims n, the owned box [lo, lo + w) and the index of its
+// first record.
+struct Box {
+    int64_t n0, n1, n2, lo0, lo1, lo2, w0, w1, w2, rec_off;
+};
+
+// The thread's index, as a value that the compiler takes to be new at each
+// call: what a tile's code derives from it is then not hoisted out of a loop
+// over tiles (some 80 such values were, and spilled).
+__device__ __forceinline__ int tile_thread()
+{
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    return tid;
+}
+
+// Stages the comparison keys of tile (bx, by, bz) of the box, with a
+// one-vertex halo, in LDS (no barrier afterwards).
 template <typename Keys, int GX, int GY>
-__device__ __forceinline__ void gradient_tile(const void *__restrict__ field, int64_t nx,
-                                              int64_t ny, int64_t nz, int64_t lo0, int64_t lo1,
-                                              int64_t lo2, int64_t w0, int64_t w1, int64_t w2,
-                                              int64_t bx, int64_t by, int64_t bz, int64_t rec_off,
-                                              uint4 *__restrict__ rec, const uint4 *__restrict__ defect8,
-                                              uint4 *__restrict__ queue, uint32_t *qcount, uint32_t qcap,
-                                              uint32_t *flags, uint32_t *__restrict__ mark, BlockShared &sh,
-                                              typename Keys::H *tile)
+__device__ __forceinline__ void stage_halo(const void *__restrict__ field, const Box &B, int64_t bx, int64_t by,
+                                           int64_t bz, int tid, uint32_t *flags, typename Keys::H *tile)
 {
     using S = Tile<GX, GY>;
-    using C = typename Keys::C;
-    const int tid = threadIdx.x;
-    if (tid == 0) sh.nlist = 0;
-    const int64_t x0 = lo0 + bx * GX - 1, y0 = lo1 + by * GY - 1, z0 = lo2 + bz - 1;
+    const int64_t nx = B.n0, ny = B.n1, nz = B.n2;
+    const int64_t x0 = B.lo0 + bx * GX - 1, y0 = B.lo1 + by * GY - 1, z0 = B.lo2 + bz - 1;
     const bool full = x0 >= 0 && y0 >= 0 && z0 >= 0 && x0 + S::HX <= nx && y0 + S::HY <= ny &&
                       z0 + S::HZ <= nz;
     bool nan = false, nan_any = false;
@@ -640,10 +667,43 @@ __device__ __forceinline__ void gradient_tile(const void *__restrict__ field, in
         }
     }
     if (flags && __ballot(nan_any) && lane_id() == 0) atomicOr(flags, (uint32_t)DMS_FLAG_NAN);
+}
+
+// A wave whose first row of the tile is mostly general vertices (a noisy
+// field) leaves the table vertices of its other rows to the general path too:
+// the table index costs every lane of a row that has one.  in, gen: whether
+// this lane's vertex of the first row lies in the box, and is general.
+__device__ __forceinline__ bool skip_tables(bool in, bool gen)
+{
+    const int n = __popcll(__ballot(in)), g = __popcll(__ballot(in && gen));
+    return g >= 32 && 2 * g > n;
+}
+
+// The table vertices of one GX x GY x 1 tile (1024 vertices, 4 per thread) of
+// a box: their records from the precomputed tables.  The other vertices are
+// handed over (Handoff).  tile_no: the tile's number in the launch.  Must be
+// entered by the whole block.
+struct TileShared {
+    uint32_t qbase, nlist;
+    uint16_t list[kTileVerts];  // general vertices of the tile (tile positions)
+};
+
+template <typename Keys, int GX, int GY>
+__device__ __forceinline__ void gradient_tile(const void *__restrict__ field, const Box &B, int64_t bx, int64_t by,
+                                              int64_t bz, uint32_t tile_no, uint4 *__restrict__ rec,
+                                              const uint4 *__restrict__ defect8, const Handoff &H, uint32_t *flags,
+                                              uint32_t *__restrict__ mark, TileShared &sh,
+                                              typename Keys::H *tile)
+{
+    using S = Tile<GX, GY>;
+    using C = typename Keys::C;
+    const int tid = threadIdx.x;
+    const int64_t w0 = B.w0, w1 = B.w1, w2 = B.w2;
+    if (tid == 0) sh.nlist = 0;
+    stage_halo<Keys, GX, GY>(field, B, bx, by, bz, tid, flags, tile);
     __syncthreads();
 
-    // pass 1: table vertices; the others are listed
-    const int64_t rbase = rec_off + (bx * GX) + w0 * ((by * GY) + w1 * bz);
+    const int64_t rbase = B.rec_off + (bx * GX) + w0 * ((by * GY) + w1 * bz);
     // a 64-wide tile: vertex k of a thread lies in column lane and row
     // wave + 4 k, the same row for the whole wave, so the row's part of the
     // LDS and record addresses stays in scalar registers
@@ -656,6 +716,7 @@ __device__ __forceinline__ void gradient_tile(const void *__restrict__ field, in
     uint32_t fw[kPer];   // the flag words of the entries
     uint32_t fbit = 0;   // 5 bits per vertex: the entry's bit in its flag word
     uint32_t state = 0;  // bit k: vertex k in the box; bit kPer + k: it has an entry
+    bool skip = false;   // uniform in the wave
 #pragma unroll
     for (int k = 0; k < kPer; ++k) {
         const int v = tid + k * kThreads;
@@ -663,12 +724,15 @@ __device__ __forceinline__ void gradient_tile(const void *__restrict__ field, in
         const int ty = GX == kWave ? wave_u + (kThreads / kWave) * k : v / GX;
         TabHit hit{nullptr, g_regular_flags, 0};
         if (bx * GX + tx < w0 && by * GY + ty < w1 && bz < w2) {
-            const int c = (tx + 1) + S::HX * ((ty + 1) + S::HY);
-            C o[14], ox;
-            gather_orders<Keys, GX, GY>(tile, c, o, ox);
-            hit = table_entry(lower_mask(o, ox), o, defect8);
+            if (!skip) {
+                const int c = (tx + 1) + S::HX * ((ty + 1) + S::HY);
+                C o[14], ox;
+                gather_orders<Keys, GX, GY>(tile, c, o, ox);
+                hit = table_entry(lower_mask(o, ox), o, defect8);
+            }
             state |= 1u << k;
         }
+        if (k == 0) skip = skip_tables(state & 1u, !hit.rec);
         if (hit.rec) state |= 1u << (kPer + k);
         const uint4 e = *(hit.rec ? hit.rec : g_regular);
         gx[k] = e.x;
@@ -696,104 +760,55 @@ __device__ __forceinline__ void gradient_tile(const void *__restrict__ field, in
     const uint32_t total = sh.nlist;
     if (total == 0) return;
 
-    if (queue && total < (uint32_t)kThreads) {
-        // reserve queue slots; the ranking below overlaps the atomic
-        if (tid == 0) sh.qbase = atomicAdd(qcount, total);
+    const Handoff Q = H;
+    if (!Q.counts) return;  // the dense kernel takes every tile
+    bool dense = total >= (uint32_t)kThreads;
+    if (!dense) {
+        // reserve queue slots; the sorting below overlaps the atomic
+        if (tid == 0) sh.qbase = atomicAdd(&Q.counts[0], total);
         const bool mine = (uint32_t)tid < total;
         const int v = mine ? sh.list[tid] : 0;
         const int tx = v % GX, ty = v / GX;
         const int c = (tx + 1) + S::HX * ((ty + 1) + S::HY);
-        C o[14], ox;
-        gather_orders<Keys, GX, GY>(tile, c, o, ox);
-        const uint32_t low = mine ? lower_mask(o, ox) : 0u;
-        const uint64_t rk = mine ? lower_ranks(o, low) : 0xffffffffffffffull;
+        uint32_t low = 0;
+        uint64_t nb_at = 0;
+        if (mine) {
+            C o[14], ox;
+            gather_orders<Keys, GX, GY>(tile, c, o, ox);
+            low = lower_mask(o, ox);
+            nb_at = sorted_neighbours(o);
+        }
         __syncthreads();
-        // queue as many as fit below qcap, so that every slot the queue
-        // kernel reads, [0, min(count, qcap)), has been written by this launch
+        // as many as fit are queued, so that every slot the queue kernel
+        // reads, [0, min(count, qcap)), has been written by this launch
         const uint32_t qb = sh.qbase;
-        const uint32_t nq = qb >= qcap ? 0u : min(total, qcap - qb);  // uniform
-        const int64_t ridx = rbase + tx + w0 * ty;
-        if ((uint32_t)tid < nq)
-            queue[qb + tid] = queue_entry(rk, ridx, size_key(low));
-        if (nq == total) return;
-        // the queue is full: pair the rest here (rare, so unsorted)
-        const bool here = (uint32_t)tid >= nq && mine;
-        if (here) {
-            uint4 r;
-            const bool crit = robins(rk, sh.T, r);
-            rec[ridx] = r;
-            if (mark && crit) mark_critical(mark, ridx);
-        }
-        return;
+        const uint32_t nq = qb >= Q.qcap ? 0u : min(total, Q.qcap - qb);  // uniform
+        if ((uint32_t)tid < nq) Q.queue[qb + tid] = queue_entry(nb_at, rbase + tx + w0 * ty, low);
+        dense = nq < total;  // listed too: the dense kernel solves all of the tile's general vertices
     }
-
-    // a dense tile: deal its general vertices into perm by size key (the key
-    // is computed twice rather than stored: LDS is kept for occupancy)
-    for (int i = tid; i < kSizeBins; i += kThreads) sh.bins[i] = 0;
-    __syncthreads();
-    for (uint32_t i = tid; i < total; i += kThreads) {
-        const int v = sh.list[i];
-        const int c = (v % GX + 1) + S::HX * ((v / GX + 1) + S::HY);
-        C o[14], ox;
-        gather_orders<Keys, GX, GY>(tile, c, o, ox);
-        atomicAdd(&sh.bins[size_key(lower_mask(o, ox))], 1u);
-    }
-    __syncthreads();
-    scan_bins(sh.bins);
-    __syncthreads();
-    for (uint32_t i = tid; i < total; i += kThreads) {
-        const int v = sh.list[i];
-        const int c = (v % GX + 1) + S::HX * ((v / GX + 1) + S::HY);
-        C o[14], ox;
-        gather_orders<Keys, GX, GY>(tile, c, o, ox);
-        sh.perm[atomicAdd(&sh.bins[size_key(lower_mask(o, ox))], 1u)] = (uint16_t)v;
-    }
-    __syncthreads();
-
-    // pass 2: general vertices by increasing lower-star size
-    for (uint32_t base = 0; base < total; base += kThreads) {
-        const uint32_t i = base + tid;
-        const bool active = i < total;
-        const int v = active ? sh.perm[i] : 0;
-        const int tx = v % GX, ty = v / GX;
-        const int c = (tx + 1) + S::HX * ((ty + 1) + S::HY);
-        C o[14], ox;
-        gather_orders<Keys, GX, GY>(tile, c, o, ox);
-        if (active) {
-            uint4 r;
-            const bool crit = process_vertex(o, ox, sh.T, r);
-            const int64_t ri = rbase + tx + w0 * ty;
-            rec[ri] = r;
-            if (mark && crit) mark_critical(mark, ri);
-        }
+    if (dense && tid == 0) {
+        const uint32_t at = atomicAdd(&Q.counts[1], 1u);
+        if (at < Q.lcap) Q.list[at] = tile_no;
     }
 }
 
 // Keys: RankKeys reads the int32 order; F32Keys / F64Keys read the values
 // (flags receives DMS_FLAG_NAN for a NaN among them).
+// Tiles in column order, z fastest: the tiles running at the same time then
+// include each tile's neighbours above and below, which read two of its
+// three halo planes, so most halo reads hit a cache (row order, with z
+// slowest, put those neighbours a whole plane of tiles apart).
 template <typename Keys, int GX, int GY>
-__global__ __launch_bounds__(kThreads, 8) void k_gradient(const void *__restrict__ field,
-                                                       int64_t nx, int64_t ny, int64_t nz,
-                                                       int64_t lo0, int64_t lo1, int64_t lo2,
-                                                       int64_t w0, int64_t w1, int64_t w2,
-                                                       int64_t bx_count, int64_t by_count,
-                                                       uint4 *__restrict__ rec,
-                                                       const uint4 *__restrict__ defect8,
-                                                       uint4 *__restrict__ queue, uint32_t *qcount,
-                                                       uint32_t qcap, uint32_t *flags,
-                                                       uint32_t *__restrict__ mark)
+__global__ __launch_bounds__(kThreads, 8) void k_gradient(const void *__restrict__ field, Box B, int64_t bx_count,
+                                                          uint4 *__restrict__ rec,
+                                                          const uint4 *__restrict__ defect8, Handoff H,
+                                                          uint32_t *flags, uint32_t *__restrict__ mark)
 {
-    __shared__ BlockShared sh;
+    __shared__ TileShared sh;
     __shared__ typename Keys::H tile[Tile<GX, GY>::kHalo];
-    load_tables(sh.T);
-    // tiles in column order, z fastest: the tiles running at the same time
-    // then include each tile's neighbours above and below, which read two of
-    // its three halo planes, so most halo reads hit a cache (row order, with
-    // z slowest, put those neighbours a whole plane of tiles apart)
     const int64_t t = blockIdx.x;
-    const int64_t bz = t % w2, col = t / w2, bx = col % bx_count, by = col / bx_count;
-    gradient_tile<Keys, GX, GY>(field, nx, ny, nz, lo0, lo1, lo2, w0, w1, w2, bx, by, bz, 0, rec, defect8,
-                                queue, qcount, qcap, flags, mark, sh, tile);
+    const int64_t bz = t % B.w2, col = t / B.w2, bx = col % bx_count, by = col / bx_count;
+    gradient_tile<Keys, GX, GY>(field, B, bx, by, bz, blockIdx.x, rec, defect8, H, flags, mark, sh, tile);
 }
 
 // Batched form: many whole fields, concatenated; one block per tile of the
@@ -802,33 +817,174 @@ __global__ __launch_bounds__(kThreads, 8) void k_gradient(const void *__restrict
 // one read, and the kernel keeps the single-field kernel's registers and LDS
 // (a persistent grid walking the tiles held the walk's 64-bit state in
 // scalar registers and spilled).
+struct BatchTiles {
+    const BatchField *fields;
+    const int64_t *tile_start;
+    const uint16_t *tile_field;
+};
+
 template <int GX, int GY>
-__global__ __launch_bounds__(kThreads, 8) void k_gradient_batch(const int32_t *__restrict__ order,
-                                                                const BatchField *__restrict__ fields,
-                                                                const int64_t *__restrict__ tile_start,
-                                                                const uint16_t *__restrict__ tile_field,
+__device__ __forceinline__ Box batch_box(const BatchTiles &L, int64_t t, int64_t &bx, int64_t &by, int64_t &bz)
+{
+    const int f = L.tile_field[t];
+    const BatchField F = L.fields[f];
+    const int64_t bxc = (F.n[0] + GX - 1) / GX;
+    // column order inside the field, as in k_gradient
+    const int64_t k = t - L.tile_start[f], col = k / F.n[2];
+    bz = k % F.n[2];
+    bx = col % bxc;
+    by = col / bxc;
+    return Box{F.n[0], F.n[1], F.n[2], 0, 0, 0, F.n[0], F.n[1], F.n[2], F.off};
+}
+
+template <int GX, int GY>
+__global__ __launch_bounds__(kThreads, 8) void k_gradient_batch(const int32_t *__restrict__ order, BatchTiles L,
                                                                 uint4 *__restrict__ rec,
-                                                                const uint4 *__restrict__ defect8,
-                                                                uint4 *__restrict__ queue,
-                                                                uint32_t *qcount, uint32_t qcap,
+                                                                const uint4 *__restrict__ defect8, Handoff H,
                                                                 uint32_t *__restrict__ mark)
 {
-    __shared__ BlockShared sh;
+    __shared__ TileShared sh;
     __shared__ int32_t tile[Tile<GX, GY>::kHalo];
-    load_tables(sh.T);
-    const int64_t t = blockIdx.x;
-    const int f = tile_field[t];
-    const BatchField F = fields[f];
-    const int64_t bxc = (F.n[0] + GX - 1) / GX, byc = (F.n[1] + GY - 1) / GY;
-    // column order inside the field, as in k_gradient
-    const int64_t k = t - tile_start[f];
-    const int64_t bz = k % F.n[2], col = k / F.n[2], bx = col % bxc, by = col / bxc;
-    gradient_tile<RankKeys, GX, GY>(order + F.off, F.n[0], F.n[1], F.n[2], 0, 0, 0, F.n[0], F.n[1], F.n[2], bx,
-                                    by, bz, F.off, rec, defect8, queue, qcount, qcap, nullptr, mark, sh,
+    int64_t bx, by, bz;
+    const Box B = batch_box<GX, GY>(L, blockIdx.x, bx, by, bz);
+    gradient_tile<RankKeys, GX, GY>(order + B.rec_off, B, bx, by, bz, blockIdx.x, rec, defect8, H, nullptr, mark, sh,
                                     tile);
 }
 
-__global__ void k_queue_reset(uint32_t *qcount) { *qcount = 0; }
+// All vertices of one tile that gradient_tile left, solved in rounds of
+// kThreads, dealt by the number of lower neighbours.  part of parts (1 or 4):
+// the quarter of the tile's positions this block takes.
+struct DenseShared {
+    StarTables T;
+    uint32_t bins[kSizeBins];
+    uint32_t crit[kTileVerts / 32];  // bit v: tile position v holds a critical cell
+    uint16_t perm[kTileVerts];       // tile positions by lower-neighbour count
+};
+
+template <typename Keys, int GX, int GY>
+__device__ __forceinline__ void dense_tile(const void *__restrict__ field, const Box &B, int64_t bx, int64_t by,
+                                           int64_t bz, int part, int parts, uint4 *__restrict__ rec,
+                                           uint32_t *__restrict__ mark, DenseShared &sh,
+                                           typename Keys::H *tile)
+{
+    using S = Tile<GX, GY>;
+    using C = typename Keys::C;
+    constexpr int kPer = kTileVerts / kThreads;
+    const int tid = tile_thread();
+    stage_halo<Keys, GX, GY>(field, B, bx, by, bz, tid, nullptr, tile);
+    if (tid < kSizeBins) sh.bins[tid] = 0;
+    if (tid < kTileVerts / 32) sh.crit[tid] = 0;
+    __syncthreads();
+    uint32_t sizes = 0;  // 8 bits per vertex: lower-neighbour count, bit 7 set for a vertex to be solved
+    bool skip = false;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const int v = tid + k * kThreads;
+        const bool mine = parts == 1 || k == part;  // uniform
+        if (k > 0 && !mine) continue;
+        const int tx = v % GX, ty = v / GX;
+        const bool in = bx * GX + tx < B.w0 && by * GY + ty < B.w1;
+        C o[14], ox;
+        gather_orders<Keys, GX, GY>(tile, (tx + 1) + S::HX * ((ty + 1) + S::HY), o, ox);
+        const uint32_t low = lower_mask(o, ox);
+        const bool gen = general_vertex(low);
+        if (k == 0) skip = skip_tables(in, gen);
+        if (mine && in && (gen || (k > 0 && skip))) {
+            const uint32_t m = (uint32_t)__popc(low);
+            sizes |= (128u | m) << (8 * k);
+            atomicAdd(&sh.bins[m], 1u);
+        }
+    }
+    __syncthreads();
+    scan_bins(sh.bins);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const uint32_t s = (sizes >> (8 * k)) & 255u;
+        if (s & 128u) sh.perm[atomicAdd(&sh.bins[s & 15u], 1u)] = (uint16_t)(tid + k * kThreads);
+    }
+    __syncthreads();
+    const uint32_t total = sh.bins[kSizeBins - 1];  // its own bin is empty: the end of the last one
+    const int64_t rbase = B.rec_off + (bx * GX) + B.w0 * ((by * GY) + B.w1 * bz);
+    for (uint32_t base = 0; base < total; base += kThreads) {
+        const uint32_t i = base + tid;
+        if (i < total) {
+            const int v = sh.perm[i];
+            const int tx = v % GX, ty = v / GX;
+            C o[14], ox;
+            gather_orders<Keys, GX, GY>(tile, (tx + 1) + S::HX * ((ty + 1) + S::HY), o, ox);
+            uint4 r;
+            if (process_vertex(o, ox, sh.T, r)) atomicOr(&sh.crit[v / 32], 1u << (v % 32));
+            rec[rbase + tx + B.w0 * ty] = r;
+        }
+    }
+    __syncthreads();
+    // the mask bits of 16 positions of a row at a time
+    if (mark && tid < kTileVerts / 16) {
+        const uint64_t bits = (sh.crit[tid / 2] >> (16 * (tid % 2))) & 0xffffu;
+        if (bits) {
+            const int v = 16 * tid;
+            const int64_t r = rbase + v % GX + B.w0 * (v / GX);
+            const uint64_t m = bits << (r & 31);
+            if ((uint32_t)m) atomicOr(&mark[r >> 5], (uint32_t)m);
+            if (m >> 32) atomicOr(&mark[(r >> 5) + 1], (uint32_t)(m >> 32));
+        }
+    }
+    __syncthreads();
+}
+
+// The listed tiles (every tile when there is no list or it overflowed), dealt
+// to a grid of at most kDenseBlocks blocks.  A list with less than a quarter
+// of a tile per block is dealt in quarter tiles, which repeat only the staging.
+constexpr int kDenseBlocks = 256 * 6;
+
+template <typename Solve>
+__device__ __forceinline__ void dense_walk(const Handoff &H, uint32_t ntiles, Solve solve)
+{
+    uint32_t n = ntiles;
+    const uint32_t *list = nullptr;
+    if (H.counts && H.counts[1] <= H.lcap) {
+        n = H.counts[1];
+        list = H.list;
+    }
+    const int parts = (uint64_t)n * 4 <= gridDim.x ? 4 : 1;
+    for (uint64_t i = blockIdx.x; i < (uint64_t)n * parts; i += gridDim.x) {
+        const uint32_t j = (uint32_t)(i / parts);
+        solve(list ? list[j] : j, (int)(i % parts), parts);
+    }
+}
+
+template <typename Keys, int GX, int GY>
+__global__ __launch_bounds__(kThreads, 6) void k_gradient_dense(const void *__restrict__ field, Box B,
+                                                                int64_t bx_count, uint32_t ntiles,
+                                                                uint4 *__restrict__ rec, Handoff H,
+                                                                uint32_t *__restrict__ mark)
+{
+    __shared__ DenseShared sh;
+    __shared__ typename Keys::H tile[Tile<GX, GY>::kHalo];
+    load_tables(sh.T);
+    dense_walk(H, ntiles, [&](uint32_t t, int part, int parts) {
+        const int64_t bz = t % B.w2, col = t / B.w2, bx = col % bx_count, by = col / bx_count;
+        dense_tile<Keys, GX, GY>(field, B, bx, by, bz, part, parts, rec, mark, sh, tile);
+    });
+}
+
+template <int GX, int GY>
+__global__ __launch_bounds__(kThreads, 6) void k_gradient_dense_batch(const int32_t *__restrict__ order, BatchTiles L,
+                                                                      uint32_t ntiles, uint4 *__restrict__ rec,
+                                                                      Handoff H, uint32_t *__restrict__ mark)
+{
+    __shared__ DenseShared sh;
+    __shared__ int32_t tile[Tile<GX, GY>::kHalo];
+    load_tables(sh.T);
+    dense_walk(H, ntiles, [&](uint32_t t, int part, int parts) {
+        int64_t bx, by, bz;
+        const Box B = batch_box<GX, GY>(L, t, bx, by, bz);
+        dense_tile<RankKeys, GX, GY>(order + B.rec_off, B, bx, by, bz, part, parts, rec, mark, sh, tile);
+    });
+}
+
+__global__ void k_queue_reset(uint32_t *counts) { counts[threadIdx.x] = 0; }
 
 __global__ void k_mark_zero(uint32_t *__restrict__ mark, int64_t words)
 {
@@ -836,15 +992,15 @@ __global__ void k_mark_zero(uint32_t *__restrict__ mark, int64_t words)
     if (i < words) mark[i] = 0u;
 }
 
-// Pairs the queued general vertices: block b takes entries
-// [b kQueueChunk, (b+1) kQueueChunk) of the filled part, sorts them by size
-// key and runs Robins' loop on them in full rounds.
-__global__ __launch_bounds__(kThreads) void k_gradient_queue(const uint4 *__restrict__ queue,
-                                                             const uint32_t *qcount, uint32_t qcap,
-                                                             uint4 *__restrict__ rec,
-                                                             uint32_t *__restrict__ mark)
+// Solves the queued general vertices: block b takes entries
+// [b kQueueChunk, (b+1) kQueueChunk) of the filled part, sorts them by the
+// number of lower neighbours and solves them in full rounds.
+__global__ __launch_bounds__(kThreads, 8) void k_gradient_queue(const uint4 *__restrict__ queue,
+                                                                const uint32_t *qcount, uint32_t qcap,
+                                                                uint4 *__restrict__ rec,
+                                                                uint32_t *__restrict__ mark)
 {
-    __shared__ SharedTables T;
+    __shared__ StarTables T;
     __shared__ uint32_t bins[kSizeBins];
     __shared__ uint16_t perm[kQueueChunk];
     const int tid = threadIdx.x;
@@ -853,28 +1009,22 @@ __global__ __launch_bounds__(kThreads) void k_gradient_queue(const uint4 *__rest
     if (start >= filled) return;  // uniform
     const uint32_t cnt = (uint32_t)min<uint64_t>(kQueueChunk, filled - start);
     load_tables(T);
-    for (int i = tid; i < kSizeBins; i += kThreads) bins[i] = 0;
+    if (tid < kSizeBins) bins[tid] = 0;
     __syncthreads();
-    for (uint32_t i = tid; i < cnt; i += kThreads) atomicAdd(&bins[min(queue[start + i].w, (uint32_t)kSizeBins - 1u)], 1u);
+    for (uint32_t i = tid; i < cnt; i += kThreads) atomicAdd(&bins[__popc(queue[start + i].w) & 15], 1u);
     __syncthreads();
     scan_bins(bins);
     __syncthreads();
     for (uint32_t i = tid; i < cnt; i += kThreads)
-        perm[atomicAdd(&bins[min(queue[start + i].w, (uint32_t)kSizeBins - 1u)], 1u)] = (uint16_t)i;
+        perm[atomicAdd(&bins[__popc(queue[start + i].w) & 15], 1u)] = (uint16_t)i;
     __syncthreads();
-    for (uint32_t base = 0; base < cnt; base += kThreads) {
-        const uint32_t i = base + tid;
-        const bool active = i < cnt;
-        uint4 e = make_uint4(0xffffffffu, 0x00ffffffu, 0u, 0u);  // no lower neighbour
-        if (active) e = queue[start + perm[i]];
-        const uint64_t rk = entry_ranks(e);
-        if (active) {
-            uint4 r;
-            const bool crit = robins(rk, T, r);
-            const int64_t ri = entry_record(e);
-            rec[ri] = r;
-            if (mark && crit) mark_critical(mark, ri);
-        }
+    for (uint32_t i = tid; i < cnt; i += kThreads) {
+        const uint4 e = queue[start + perm[i]];
+        uint4 r;
+        const bool crit = solve_star(entry_neighbours(e), e.w & 0x3fffu, T, r);
+        const int64_t ri = entry_record(e);
+        rec[ri] = r;
+        if (mark && crit) mark_critical(mark, ri);
     }
 }
 
@@ -906,7 +1056,7 @@ __device__ void lehmer_decode(uint32_t code, uint32_t *rank)
 // 13 - i (bit i of side), ordered by the permutation with Lehmer code `code`.
 __global__ __launch_bounds__(kThreads) void k_regular_table()
 {
-    __shared__ SharedTables T;
+    __shared__ StarTables T;
     load_tables(T);
     __syncthreads();
     const int idx = blockIdx.x * kThreads + threadIdx.x;  // a wave covers 64 aligned entries
@@ -939,7 +1089,7 @@ __global__ __launch_bounds__(kThreads) void k_regular_table()
 template <bool kEight>
 __global__ __launch_bounds__(kThreads) void k_defect_table(uint4 *table)
 {
-    __shared__ SharedTables T;
+    __shared__ StarTables T;
     load_tables(T);
     __syncthreads();
     constexpr int N = kEight ? 8 : 7;
@@ -1031,78 +1181,70 @@ int tables_ready()
 }
 
 
-// Queue of general vertices: a counter, then qcap 16-byte entries; room for
-// one vertex in 16 plus a chunk.
-static uint32_t queue_cap(int64_t owned)
+// Workspace: 256 bytes of counters, then room for one vertex in 16 plus a
+// chunk as 16-byte queue entries, of which the last 1/256 of a vertex each
+// hold the list of dense tiles (4 bytes a tile).  A dense tile has at least
+// kThreads vertices, so the list has room for all of them and for three times
+// as many tiles that found the queue full.
+static int64_t workspace_slots(int64_t owned)
 {
     const int64_t c = owned / 16 + kQueueChunk;
-    return (uint32_t)(c < 0x7fffffffLL ? c : 0x7fffffffLL);
+    return c < 0x7fffffffLL ? c : 0x7fffffffLL;
 }
 
-size_t gradient_workspace_size(int64_t owned) { return 256 + (size_t)queue_cap(owned) * sizeof(uint4); }
+size_t gradient_workspace_size(int64_t owned) { return 256 + (size_t)workspace_slots(owned) * sizeof(uint4); }
 
-// Resets the queue counter; returns (queue, counter, capacity) carved from ws
-// (all null / 0 when ws is null: every tile then pairs its own vertices).
-static void queue_begin(char *ws, int64_t owned, hipStream_t s, uint4 **queue, uint32_t **qcount,
-                        uint32_t *qcap)
+// Carves the workspace and resets its counters (all null when ws is null).
+static Handoff handoff_begin(char *ws, int64_t owned, hipStream_t s)
 {
-    *queue = nullptr;
-    *qcount = nullptr;
-    *qcap = 0;
-    if (!ws) return;
-    *qcount = (uint32_t *)ws;
-    *queue = (uint4 *)(ws + 256);
-    *qcap = queue_cap(owned);
-    hipLaunchKernelGGL(k_queue_reset, dim3(1), dim3(1), 0, s, *qcount);
+    Handoff H{nullptr, nullptr, nullptr, 0, 0};
+    if (!ws) return H;
+    const int64_t slots = workspace_slots(owned);
+    int64_t lslots = owned / kThreads + 16;
+    if (lslots > slots / 2) lslots = slots / 2;
+    H.counts = (uint32_t *)ws;
+    H.queue = (uint4 *)(ws + 256);
+    H.qcap = (uint32_t)(slots - lslots);
+    H.list = (uint32_t *)(H.queue + H.qcap);
+    H.lcap = (uint32_t)(lslots < 0x1fffffff ? 4 * lslots : 0x7fffffff);
+    hipLaunchKernelGGL(k_queue_reset, dim3(1), dim3(2), 0, s, H.counts);
+    return H;
 }
 
-static void queue_finish(const uint4 *queue, const uint32_t *qcount, uint32_t qcap, uint32_t *rec,
-                         uint32_t *mark, hipStream_t s)
+static void queue_finish(const Handoff &H, uint32_t *rec, uint32_t *mark, hipStream_t s)
 {
-    if (!queue) return;
-    const unsigned blocks = (unsigned)((qcap + kQueueChunk - 1) / kQueueChunk);
-    hipLaunchKernelGGL(k_gradient_queue, dim3(blocks), dim3(kThreads), 0, s, queue, qcount, qcap,
+    if (!H.counts) return;
+    const unsigned blocks = (unsigned)(((int64_t)H.qcap + kQueueChunk - 1) / kQueueChunk);
+    hipLaunchKernelGGL(k_gradient_queue, dim3(blocks), dim3(kThreads), 0, s, H.queue, H.counts, H.qcap,
                        (uint4 *)rec, mark);
 }
 
+static unsigned dense_blocks(int64_t ntiles) { return (unsigned)(4 * ntiles < kDenseBlocks ? 4 * ntiles : kDenseBlocks); }
+
 template <typename Keys>
-static int launch_gradient_keys(int variant, const void *field, const int64_t *dims, const int64_t *lo,
+static int launch_gradient_keys(const void *field, const int64_t *dims, const int64_t *lo,
                                 const int64_t *hi, uint32_t *rec, uint32_t *mark, char *ws, uint32_t *flags,
                                 hipStream_t s)
 {
-    const int64_t w0 = hi[0] - lo[0], w1 = hi[1] - lo[1], w2 = hi[2] - lo[2];
-    if (w0 == 0 || w1 == 0 || w2 == 0) return DMS_OK;
+    const Box B{dims[0], dims[1], dims[2], lo[0], lo[1], lo[2], hi[0] - lo[0], hi[1] - lo[1], hi[2] - lo[2], 0};
+    if (B.w0 == 0 || B.w1 == 0 || B.w2 == 0) return DMS_OK;
+    const int64_t owned = B.w0 * B.w1 * B.w2;
     if (mark) {
-        const int64_t words = (w0 * w1 * w2 + 31) / 32;
+        const int64_t words = (owned + 31) / 32;
         hipLaunchKernelGGL(k_mark_zero, dim3((unsigned)((words + kThreads - 1) / kThreads)), dim3(kThreads), 0, s,
                            mark, words);
     }
-    const int gx = kTileX[variant], gy = kTileVerts / gx;
-    const int64_t bxc = (w0 + gx - 1) / gx, byc = (w1 + gy - 1) / gy;
-    const int64_t blocks = bxc * byc * w2;
+    constexpr int kGX = kTileX[0], kGY = kTileVerts / kGX;
+    const int64_t bxc = (B.w0 + kGX - 1) / kGX, byc = (B.w1 + kGY - 1) / kGY;
+    const int64_t blocks = bxc * byc * B.w2;
     if (blocks > 2147483647LL) return DMS_E_SIZE;
-    const uint4 *d8 = defect8_table();
-    uint4 *queue;
-    uint32_t *qcount, qcap;
-    queue_begin(ws, w0 * w1 * w2, s, &queue, &qcount, &qcap);
-#define DMS_LAUNCH(GXV)                                                                              \
-    hipLaunchKernelGGL((k_gradient<Keys, GXV, kTileVerts / GXV>), dim3((unsigned)blocks), dim3(kThreads), \
-                       0, s, field, dims[0], dims[1], dims[2], lo[0], lo[1], lo[2], w0, w1, w2, bxc, byc, \
-                       (uint4 *)rec, d8, queue, qcount, qcap, flags, mark)
-    switch (variant) {
-    case 0: DMS_LAUNCH(64); break;
-    case 1: DMS_LAUNCH(32); break;
-    default: DMS_LAUNCH(16); break;
-    }
-#undef DMS_LAUNCH
-    queue_finish(queue, qcount, qcap, rec, mark, s);
+    const Handoff H = handoff_begin(ws, owned, s);
+    hipLaunchKernelGGL((k_gradient<Keys, kGX, kGY>), dim3((unsigned)blocks), dim3(kThreads), 0, s, field, B, bxc,
+                       (uint4 *)rec, defect8_table(), H, flags, mark);
+    hipLaunchKernelGGL((k_gradient_dense<Keys, kGX, kGY>), dim3(dense_blocks(blocks)), dim3(kThreads), 0, s, field,
+                       B, bxc, (uint32_t)blocks, (uint4 *)rec, H, mark);
+    queue_finish(H, rec, mark, s);
     return launch_status();
-}
-
-int launch_gradient(int variant, const int32_t *order, const int64_t *dims, const int64_t *lo,
-                    const int64_t *hi, uint32_t *rec, uint32_t *mark, char *ws, hipStream_t s)
-{
-    return launch_gradient_keys<RankKeys>(variant, order, dims, lo, hi, rec, mark, ws, nullptr, s);
 }
 
 int launch_gradient_batch(int variant, const int32_t *order, const BatchField *fields, int nfields,
@@ -1118,19 +1260,20 @@ int launch_gradient_batch(int variant, const int32_t *order, const BatchField *f
                            mark, words);
     }
     const uint4 *d8 = defect8_table();
-    uint4 *queue;
-    uint32_t *qcount, qcap;
-    queue_begin(ws, total_verts, s, &queue, &qcount, &qcap);
-#define DMS_LAUNCH(GXV)                                                                               \
-    hipLaunchKernelGGL((k_gradient_batch<GXV, kTileVerts / GXV>), dim3((unsigned)total_tiles), dim3(kThreads), \
-                       0, s, order, fields, tile_start, tile_field, (uint4 *)rec, d8, queue, qcount, qcap, mark)
+    const Handoff H = handoff_begin(ws, total_verts, s);
+    const BatchTiles L{fields, tile_start, tile_field};
+#define DMS_LAUNCH(GXV)                                                                                             \
+    hipLaunchKernelGGL((k_gradient_batch<GXV, kTileVerts / GXV>), dim3((unsigned)total_tiles), dim3(kThreads), 0, s, \
+                       order, L, (uint4 *)rec, d8, H, mark);                                                         \
+    hipLaunchKernelGGL((k_gradient_dense_batch<GXV, kTileVerts / GXV>), dim3(dense_blocks(total_tiles)),             \
+                       dim3(kThreads), 0, s, order, L, (uint32_t)total_tiles, (uint4 *)rec, H, mark)
     switch (variant) {
     case 0: DMS_LAUNCH(64); break;
     case 1: DMS_LAUNCH(32); break;
     default: DMS_LAUNCH(16); break;
     }
 #undef DMS_LAUNCH
-    queue_finish(queue, qcount, qcap, rec, mark, s);
+    queue_finish(H, rec, mark, s);
     return launch_status();
 }
 
@@ -1156,7 +1299,8 @@ extern "C" int dms_discrete_gradient(const int32_t *order, const int64_t dims[3]
     if (!order || !rec) return DMS_E_ARG;
     if (workspace && workspace_bytes < gradient_workspace_size(w0 * w1 * w2)) return DMS_E_WORKSPACE;
     if (const int st = tables_ready()) return st;
-    return launch_gradient(0, order, dims, lo, hi, rec, critical_mask, (char *)workspace, (hipStream_t)stream);
+    return launch_gradient_keys<RankKeys>(order, dims, lo, hi, rec, critical_mask, (char *)workspace, nullptr,
+                                          (hipStream_t)stream);
 }
 
 extern "C" int dms_discrete_gradient_values(const void *values, int dtype, const int64_t dims[3],
@@ -1174,10 +1318,10 @@ extern "C" int dms_discrete_gradient_values(const void *values, int dtype, const
     if (workspace && workspace_bytes < gradient_workspace_size(w0 * w1 * w2)) return DMS_E_WORKSPACE;
     if (const int st = tables_ready()) return st;
     if (dtype == DMS_F32)
-        return launch_gradient_keys<F32Keys>(0, values, dims, lo, hi, rec, critical_mask, (char *)workspace,
+        return launch_gradient_keys<F32Keys>(values, dims, lo, hi, rec, critical_mask, (char *)workspace,
                                              dev_flags,
                                              (hipStream_t)stream);
-    return launch_gradient_keys<F64Keys>(0, values, dims, lo, hi, rec, critical_mask, (char *)workspace,
+    return launch_gradient_keys<F64Keys>(values, dims, lo, hi, rec, critical_mask, (char *)workspace,
                                          dev_flags,
                                          (hipStream_t)stream);
 }

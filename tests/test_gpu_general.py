@@ -1,0 +1,66 @@
+"""The vertices that no lower-star table covers, through every route: queued
+by a sparse tile, a listed (dense) tile, a listed tile dealt in quarters, a
+full queue, a full list, and no workspace at all.  Records and the critical
+mask must equal the CPU oracle's exactly."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2505_21266_amd as dms
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+# tiles hold 64 x 16 x 1 vertices and 256 general ones make a tile dense
+SHAPES = [
+    (1, 1, 5000),   # one vertex a tile: the queue fills, then the list
+    (3, 2, 900),    # six vertices a tile: the queue fills, the list does not
+    (16, 16, 96),   # 256 vertices a tile, just below and at the threshold
+    (64, 16, 5),    # a few full tiles, dealt in quarters
+    (67, 18, 31),   # ragged tiles beside full ones
+    (64, 16, 450),  # more full tiles than a quarter of the dense grid
+]
+
+
+def _field(dims, kind):
+    nx, ny, nz = dims
+    rng = np.random.default_rng(nx + 7 * ny + 31 * nz)
+    if kind == "noise":
+        return rng.random((nz, ny, nx), dtype=np.float32)
+    if kind == "ties":
+        return rng.integers(0, 4, (nz, ny, nx)).astype(np.float32)
+    # peaks: most vertices beside a few that exceed all 14 neighbours
+    v = rng.random((nz, ny, nx))
+    v[::2, ::2, ::2] += 2.0
+    return v
+
+
+def _mask_bits(mask, n):
+    words = mask.cpu().numpy().view(np.uint32)
+    return np.unpackbits(words.view(np.uint8), bitorder="little")[:n].astype(bool)
+
+
+@pytest.mark.parametrize("dims", SHAPES)
+@pytest.mark.parametrize("kind", ["noise", "ties", "peaks"])
+def test_general_vertices(dims, kind):
+    v = _field(dims, kind)
+    o = oracle.order(v)
+    want, _, _ = oracle.lower_stars(o, dims)
+    lists, _ = oracle.critical_simplices(want, dims)
+    n = o.size
+    flagged = np.zeros(n, bool)
+    for codes in lists:
+        flagged[codes >> 8] = True
+    print("general vertices", dims, kind, flush=True)
+    og = torch.from_numpy(o).cuda().reshape(dims[::-1])
+    vg = torch.from_numpy(v).cuda()
+    for queue in (True, False):
+        mask = dms.critical_mask(n, og.device)
+        got = dms.discrete_gradient(og, queue=queue, mask=mask)
+        assert (got.cpu().numpy().view(np.uint32) == want).all(), queue
+        assert (_mask_bits(mask, n) == flagged).all(), queue
+        mask = dms.critical_mask(n, og.device)
+        got = dms.discrete_gradient_values(vg, queue=queue, mask=mask)
+        assert (got.cpu().numpy().view(np.uint32) == want).all(), queue
+        assert (_mask_bits(mask, n) == flagged).all(), queue

@@ -111,17 +111,44 @@ __device__ __forceinline__ uint32_t nib(uint64_t packed, int i) { return (uint32
 //  F32Keys / F64Keys: the halo holds order-preserving unsigned keys of the
 //    values (-0.0 as +0.0); a comparison value is key << 4 | slot, where the
 //    slot orders x and its neighbours by id (neighbours 0..6 precede x, 7..13
-//    follow it), so equal values break ties by id.
+//    follow it), so equal values break ties by id.  The 36 bits of F32Keys
+//    are held in a double, whose comparisons and minima are single
+//    instructions at the rate of the 32-bit ones (64-bit integers have no
+//    minimum instruction).
 // Id-order slot of neighbour e relative to x (x itself is slot 7).
 __device__ __forceinline__ constexpr int id_slot(int e) { return e < 7 ? e : e + 1; }
 
+// The 36-bit integer high4 << 32 | low32 as a double (2^52 plus it, so that
+// doubles compare like the integers).
+__device__ __forceinline__ double packed36(uint32_t high4, uint32_t low32)
+{
+    return __longlong_as_double((long long)((uint64_t)(0x43300000u | high4) << 32 | low32));
+}
+
+// Minimum and maximum of two such doubles, in one instruction each (none is
+// a NaN, which the language's own min and max would have to provide for).
+__device__ __forceinline__ double min_packed(double a, double b)
+{
+    double r;
+    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ double max_packed(double a, double b)
+{
+    double r;
+    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
 template <typename C>
 __device__ __forceinline__ C cmin(C a, C b) { return b < a ? b : a; }
+template <>
+__device__ __forceinline__ double cmin<double>(double a, double b) { return min_packed(a, b); }
 
 // A comparison value above every real one.
 template <typename C> __device__ __forceinline__ constexpr C c_highest();
 template <> __device__ __forceinline__ constexpr int32_t c_highest<int32_t>() { return 0x7fffffff; }
-template <> __device__ __forceinline__ constexpr uint64_t c_highest<uint64_t>() { return ~0ull; }
+template <> __device__ __forceinline__ constexpr double c_highest<double>() { return 9007199254740992.0; }
 template <> __device__ __forceinline__ constexpr unsigned __int128 c_highest<unsigned __int128>()
 {
     return ~(unsigned __int128)0;
@@ -137,14 +164,19 @@ struct RankKeys {
         return ((const int32_t *)f)[i];
     }
     __device__ static C cmp(H h, int) { return h; }
+    // order << 4 | e, with the order's sign bit flipped (any int32 labelling)
+    __device__ static double sort_key(C o, int e) { return packed36(((uint32_t)o >> 28) ^ 8u, (uint32_t)o << 4 | (uint32_t)e); }
+    static constexpr bool kSlots = false;
 };
 
 struct F32Keys {
     using H = uint32_t;
-    using C = uint64_t;
-    static constexpr H kAbsentH = 0xffffffffu;  // a NaN's key: never a valid input
+    using C = double;
+    static constexpr H kAbsentH = 0xffffffffu;  // a NaN's key: never a valid input, above every valid one
     __device__ static H load(const void *f, int64_t i, bool &nan) { return key_of(((const float *)f)[i], nan); }
-    __device__ static C cmp(H h, int slot) { return h == kAbsentH ? c_highest<C>() : ((C)h << 4) | (C)slot; }
+    __device__ static C cmp(H h, int slot) { return packed36(h >> 28, h << 4 | (uint32_t)slot); }
+    __device__ static double sort_key(C o, int) { return o; }
+    static constexpr bool kSlots = true;  // the low four bits name the slot, not the neighbour
 };
 
 struct F64Keys {
@@ -165,25 +197,71 @@ __device__ __forceinline__ uint32_t lower_mask(const C *o, C ox)
     return low;
 }
 
-// The 14 neighbours in increasing order, 4 bits each (neighbours outside the
-// grid compare above all others, by index among themselves).
-template <typename C>
-__device__ __forceinline__ uint64_t sorted_neighbours(const C *o)
+// Batcher's odd-even merge sort of 16 inputs, without the comparators that
+// touch the last two (which would hold the largest values): 53 comparators.
+struct Comparators {
+    uint8_t lo[64], hi[64];
+    int n;
+};
+
+constexpr Comparators make_comparators(int inputs)
 {
-    uint32_t r[14];
-#pragma unroll
-    for (int e = 0; e < 14; ++e) r[e] = (uint32_t)e;
-#pragma unroll
-    for (int a = 0; a < 14; ++a)
-#pragma unroll
-        for (int b = a + 1; b < 14; ++b) {
-            const uint32_t c = o[b] < o[a] ? 1u : 0u;
-            r[a] += c;
-            r[b] -= c;
-        }
+    Comparators N{};
+    for (int p = 1; p < 16; p *= 2)
+        for (int k = p; k >= 1; k /= 2)
+            for (int j = k % p; j + k < 16; j += 2 * k)
+                for (int i = 0; i < k; ++i)
+                    if ((i + j) / (2 * p) == (i + j + k) / (2 * p) && i + j + k < inputs) {
+                        N.lo[N.n] = (uint8_t)(i + j);
+                        N.hi[N.n++] = (uint8_t)(i + j + k);
+                    }
+    return N;
+}
+
+constexpr Comparators kSort14 = make_comparators(14);
+static_assert(kSort14.n == 53, "comparators of 14 inputs");
+
+// The 14 neighbours in increasing order, 4 bits each; neighbours outside the
+// grid compare above all others.  Ranks and single-precision values are sorted
+// as doubles that carry the neighbour in their low bits, a minimum and a
+// maximum per comparator (about 180 instructions; counting each neighbour's
+// predecessors over the 91 pairs takes 330).  Double-precision values have no
+// room for it and are counted.
+template <typename Keys>
+__device__ __forceinline__ uint64_t sorted_neighbours(const typename Keys::C *o)
+{
     uint64_t at = 0;
+    if constexpr (sizeof(typename Keys::C) <= 8) {
+        double p[14];
 #pragma unroll
-    for (int e = 1; e < 14; ++e) at |= (uint64_t)e << (4 * r[e]);
+        for (int e = 0; e < 14; ++e) p[e] = Keys::sort_key(o[e], e);
+#pragma unroll
+        for (int c = 0; c < kSort14.n; ++c) {
+            const double a = p[kSort14.lo[c]], b = p[kSort14.hi[c]];
+            p[kSort14.lo[c]] = min_packed(a, b);
+            p[kSort14.hi[c]] = max_packed(a, b);
+        }
+        uint32_t w[2] = {0, 0};
+#pragma unroll
+        for (int r = 0; r < 14; ++r)
+            w[r / 8] |= ((uint32_t)__double_as_longlong(p[r]) & 15u) << (4 * (r % 8));
+        at = (uint64_t)w[1] << 32 | w[0];
+        if constexpr (Keys::kSlots) at -= (at >> 3) & 0x1111111111111111ull;  // slot 8..14 is neighbour 7..13
+    } else {
+        uint32_t r[14];
+#pragma unroll
+        for (int e = 0; e < 14; ++e) r[e] = (uint32_t)e;
+#pragma unroll
+        for (int a = 0; a < 14; ++a)
+#pragma unroll
+            for (int b = a + 1; b < 14; ++b) {
+                const uint32_t c = o[b] < o[a] ? 1u : 0u;
+                r[a] += c;
+                r[b] -= c;
+            }
+#pragma unroll
+        for (int e = 1; e < 14; ++e) at |= (uint64_t)e << (4 * r[e]);
+    }
     return at;
 }
 
@@ -237,7 +315,7 @@ __device__ __forceinline__ uint32_t smallest_triangle(uint32_t S, const uint32_t
 //
 // Bound by vector-instruction issue: 63 instructions per node reached beyond
 // d's neighbours (39 of them the search), 22 per tet, 47 per critical
-// triangle, about 200 once, beside the 290 of sorted_neighbours.  A wave of
+// triangle, about 200 once, beside sorted_neighbours.  A wave of
 // white noise reaches 4.9 nodes and strips 8.3 tets (its longest lane, dealt
 // by lower-neighbour count).  It replaced a loop over single pairs that kept
 // 60-bit sets of the unpaired cells and searched all of them each time (about
@@ -355,10 +433,11 @@ __device__ __forceinline__ bool solve_star(uint64_t nb_at, uint32_t low, const S
 }
 
 // From the orders of x and its neighbours.
-template <typename C>
-__device__ __forceinline__ bool process_vertex(const C *o, C ox, const StarTables &T, uint4 &out)
+template <typename Keys>
+__device__ __forceinline__ bool process_vertex(const typename Keys::C *o, typename Keys::C ox, const StarTables &T,
+                                               uint4 &out)
 {
-    return solve_star(sorted_neighbours(o), lower_mask(o, ox), T, out);
+    return solve_star(sorted_neighbours<Keys>(o), lower_mask(o, ox), T, out);
 }
 
 // ---------------------------------------------------------------------------
@@ -776,7 +855,7 @@ __device__ __forceinline__ void gradient_tile(const void *__restrict__ field, co
             C o[14], ox;
             gather_orders<Keys, GX, GY>(tile, c, o, ox);
             low = lower_mask(o, ox);
-            nb_at = sorted_neighbours(o);
+            nb_at = sorted_neighbours<Keys>(o);
         }
         __syncthreads();
         // as many as fit are queued, so that every slot the queue kernel
@@ -914,7 +993,7 @@ __device__ __forceinline__ void dense_tile(const void *__restrict__ field, const
             C o[14], ox;
             gather_orders<Keys, GX, GY>(tile, (tx + 1) + S::HX * ((ty + 1) + S::HY), o, ox);
             uint4 r;
-            if (process_vertex(o, ox, sh.T, r)) atomicOr(&sh.crit[v / 32], 1u << (v % 32));
+            if (process_vertex<Keys>(o, ox, sh.T, r)) atomicOr(&sh.crit[v / 32], 1u << (v % 32));
             rec[rbase + tx + B.w0 * ty] = r;
         }
     }
@@ -1072,7 +1151,7 @@ __global__ __launch_bounds__(kThreads) void k_regular_table()
             o[13 - lowm] = 100 + i;  // above x
         }
         uint4 r;
-        crit = process_vertex(o, 50, T, r);
+        crit = process_vertex<RankKeys>(o, 50, T, r);
         g_regular[idx] = r;
     }
     const uint64_t m = __ballot(crit);
@@ -1116,7 +1195,7 @@ __global__ __launch_bounds__(kThreads) void k_defect_table(uint4 *table)
                 o[((side >> i) & 1u) ? 13 - i : i] = (int32_t)rank[i];
             }
             if (kEight) o[j] = (int32_t)rank[7];
-            crit = process_vertex(o, 50, T, r);
+            crit = process_vertex<RankKeys>(o, 50, T, r);
         }
         table[idx] = r;
     }

@@ -324,22 +324,22 @@ __device__ __forceinline__ uint32_t wave_prefix(CT (*wh)[kRadix])
 // same bytes (the phases are separated by a barrier).
 // A and B of at most 4 bytes each are staged packed in one 64-bit word (a in
 // the low half): one LDS write and one read per item instead of two each.
-template <typename A, typename B, int kThr = kThreads>
+template <typename A, typename B, int kThr = kThreads, int kIt = kItems>
 union Staging {
     struct {
-        A a[kThr * kItems];
-        B b[kThr * kItems];
+        A a[kThr * kIt];
+        B b[kThr * kIt];
     } st;
-    uint64_t ab[kThr * kItems];
+    uint64_t ab[kThr * kIt];
     uint64_t mk[kThr / kWave][kRadix];
-    uint16_t ftab[kFieldTable];  // a field pass's coarse field table, while ranking by ballots
+    uint16_t ftab[kIt == kItems ? kFieldTable : 1];  // a field pass's coarse field table, while ranking by ballots
 };
 
 template <typename A, typename B>
 constexpr bool kPacked = sizeof(A) <= 4 && sizeof(B) <= 4;
 
-template <typename A, typename B, int kThr>
-__device__ __forceinline__ void stage_put(Staging<A, B, kThr> &S, uint32_t pos, A a, B b)
+template <typename A, typename B, int kThr, int kIt>
+__device__ __forceinline__ void stage_put(Staging<A, B, kThr, kIt> &S, uint32_t pos, A a, B b)
 {
     if constexpr (kPacked<A, B>) {
         S.ab[pos] = (uint64_t)(uint32_t)b << 32 | (uint64_t)a;
@@ -349,8 +349,8 @@ __device__ __forceinline__ void stage_put(Staging<A, B, kThr> &S, uint32_t pos, 
     }
 }
 
-template <typename A, typename B, int kThr>
-__device__ __forceinline__ void stage_get(const Staging<A, B, kThr> &S, int p, A &a, B &b)
+template <typename A, typename B, int kThr, int kIt>
+__device__ __forceinline__ void stage_get(const Staging<A, B, kThr, kIt> &S, int p, A &a, B &b)
 {
     if constexpr (kPacked<A, B>) {
         const uint64_t v = S.ab[p];
@@ -362,8 +362,8 @@ __device__ __forceinline__ void stage_get(const Staging<A, B, kThr> &S, int p, A
     }
 }
 
-template <typename A, typename B, int kThr>
-__device__ __forceinline__ void zero_masks(Staging<A, B, kThr> &S)
+template <typename A, typename B, int kThr, int kIt>
+__device__ __forceinline__ void zero_masks(Staging<A, B, kThr, kIt> &S)
 {
     for (int i = threadIdx.x; i < (kThr / kWave) * kRadix; i += kThr) (&S.mk[0][0])[i] = 0ull;
 }
@@ -755,6 +755,293 @@ __global__ __launch_bounds__(kInvThreads) void k_invert_window(const ID *__restr
     for (int i = threadIdx.x; i < cnt; i += kInvThreads) order[base + i] = win[i];
 }
 
+// ---------------------------------------------------------------------------
+// Short inputs.  A pass over few keys is launches, not bytes: at 2^18 keys the
+// kernels above take 25 us a pass in five launches, most of it gaps and
+// half-empty grids.  Up to kBlockKeys keys one block does every pass in LDS;
+// up to kShortKeys a pass is two launches over tiles of 2048, 4096 or 8192
+// keys, each scatter block summing the digit counts of all tiles itself (at
+// most kShortTiles of them: 512 took as long as the three scan launches that
+// it replaces), and the last pass writes order[id] directly (the array fits
+// the caches).  Keys keep all their bytes: the digit of pass p is byte p.
+// The whole order, before and after: 7680 float32 85 -> 27 us, 2^18 98 -> 42,
+// 2^20 114 -> 71, 2^21 126 -> 106 us; float64 158 -> 45, 187 -> 91, 228 -> 140,
+// 247 -> 219 us.  Past 2^21 keys the passes above are the faster ones (their
+// keys shrink and their scan is spread over the chip).
+
+// Element type and initial key of item i (kField: the field index goes above
+// the float32 key).
+template <typename V, typename K>
+__device__ __forceinline__ K short_key(V v, int64_t i, const int64_t *foff, int nfields, bool &nan)
+{
+    K k = (K)key_of(v, nan);
+    if constexpr (sizeof(V) < sizeof(K)) k |= (K)field_of(foff, nfields, i) << 32;
+    return k;
+}
+
+// Position pos of vertex id, relative to its field's first vertex (batches:
+// the key holds the field).
+template <typename V, typename K>
+__device__ __forceinline__ int32_t short_rank(uint32_t pos, K key, const int64_t *foff)
+{
+    if constexpr (sizeof(V) < sizeof(K)) return (int32_t)((int64_t)pos - foff[(uint32_t)(key >> 32)]);
+    return (int32_t)pos;
+}
+
+// All passes of n <= kThr * kIt keys in one block.
+constexpr int kBlockThreads = 1024;
+constexpr int kBlockItems = 8;
+constexpr int kBlockKeys = kBlockThreads * kBlockItems;
+
+template <typename V, typename K>
+__global__ __launch_bounds__(kBlockThreads) void k_order_block(const V *__restrict__ values, int n, int passes,
+                                                               int32_t *__restrict__ order, uint32_t *flags,
+                                                               const int64_t *foff, int nfields)
+{
+    constexpr int kW = kBlockThreads / kWave;
+    __shared__ uint16_t whist[kW][kRadix];
+    __shared__ union {
+        uint64_t mk[kW][kRadix];
+        struct {
+            K key[kBlockKeys];
+            uint16_t id[kBlockKeys];
+        } st;
+    } S;
+    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
+    const int first = wave * (kBlockItems * kWave) + lane;
+    K key[kBlockItems];
+    uint32_t id[kBlockItems];
+    bool nan_any = false;
+#pragma unroll
+    for (int k = 0; k < kBlockItems; ++k) {
+        const int li = first + k * kWave, at = li < n ? li : n - 1;
+        bool nan;
+        key[k] = short_key<V, K>(values[at], at, foff, nfields, nan);
+        nan_any |= nan;
+        id[k] = (uint32_t)li;
+    }
+    if (__ballot(nan_any) && lane == 0) atomicOr(flags, (uint32_t)DMS_FLAG_NAN);
+    for (int p = 0; p < passes; ++p) {
+        const int shift = 8 * p;
+        for (int i = tid; i < kW * kRadix; i += kBlockThreads) {
+            (&whist[0][0])[i] = 0;
+            (&S.mk[0][0])[i] = 0ull;
+        }
+        __syncthreads();
+        uint32_t rank[kBlockItems];
+#pragma unroll
+        for (int k = 0; k < kBlockItems; ++k)
+            rank[k] = wave_rank<true>((uint32_t)(key[k] >> shift) & (kRadix - 1), first + k * kWave < n, whist[wave],
+                                      S.mk[wave]);
+        __syncthreads();
+        uint32_t total;
+        const uint32_t start =
+            block_exclusive_scan<uint32_t, kBlockThreads>(wave_prefix<kBlockThreads>(whist), &total);
+        if (tid < kRadix) {
+#pragma unroll
+            for (int w = 0; w < kW; ++w) whist[w][tid] = (uint16_t)(whist[w][tid] + start);
+        }
+        __syncthreads();
+        if (p == passes - 1) {
+#pragma unroll
+            for (int k = 0; k < kBlockItems; ++k)
+                if (first + k * kWave < n) {
+                    const uint32_t pos = whist[wave][(uint32_t)(key[k] >> shift) & (kRadix - 1)] + rank[k];
+                    order[id[k]] = short_rank<V, K>(pos, key[k], foff);
+                }
+            return;
+        }
+#pragma unroll
+        for (int k = 0; k < kBlockItems; ++k)
+            if (first + k * kWave < n) {
+                const uint32_t pos = whist[wave][(uint32_t)(key[k] >> shift) & (kRadix - 1)] + rank[k];
+                S.st.key[pos] = key[k];
+                S.st.id[pos] = (uint16_t)id[k];
+            }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kBlockItems; ++k) {
+            const int li = first + k * kWave, at = li < n ? li : n - 1;
+            key[k] = S.st.key[at];
+            id[k] = S.st.id[at];
+        }
+        __syncthreads();
+    }
+}
+
+constexpr int kShortThreads = 512;
+constexpr int kShortTiles = 256;
+// keys of a tile of kIt items a thread, and the most keys sorted in such tiles
+constexpr int short_tile(int kIt) { return kShortThreads * kIt; }
+constexpr int64_t short_keys(int kIt) { return (int64_t)short_tile(kIt) * kShortTiles; }
+constexpr int64_t kShortKeys = short_keys(16);
+static_assert(short_tile(16) <= 65535 && 2 * short_tile(4) == kTile, "16-bit counts in the long passes' space");
+
+// Digit counts of one tile: counts[tile * kRadix + digit].
+template <typename V, typename K, bool kFirst, int kIt>
+__global__ __launch_bounds__(kShortThreads) void k_short_hist(const void *__restrict__ src, int n, int shift,
+                                                              uint16_t *__restrict__ counts, uint32_t *flags,
+                                                              const int64_t *foff, int nfields)
+{
+    __shared__ HistRows hist;
+    const int tid = threadIdx.x, lane = tid % kWave;
+    const int t0 = blockIdx.x * short_tile(kIt);
+    using R = SrcT<V, K, kFirst>;
+    R raw[kIt];
+#pragma unroll
+    for (int k = 0; k < kIt; ++k) {
+        const int at = t0 + k * kShortThreads + tid;
+        raw[k] = ((const R *)src)[at < n ? at : n - 1];
+    }
+    for (int i = tid; i < kCopies * (kRadix + 1); i += kShortThreads) (&hist[0][0])[i] = 0;
+    __syncthreads();
+    bool nan_any = false;
+#pragma unroll
+    for (int k = 0; k < kIt; ++k) {
+        const int at = t0 + k * kShortThreads + tid;
+        bool nan = false;
+        K key;
+        if constexpr (kFirst) key = short_key<V, K>(raw[k], at < n ? at : n - 1, foff, nfields, nan);
+        else key = raw[k];
+        nan_any |= nan;
+        hist_add(hist, (uint32_t)(key >> shift) & (kRadix - 1), at < n);
+    }
+    __syncthreads();
+    if (kFirst && __ballot(nan_any) && lane == 0) atomicOr(flags, (uint32_t)DMS_FLAG_NAN);
+    if (tid >= kRadix) return;
+    uint32_t tot = 0;
+#pragma unroll
+    for (int c = 0; c < kCopies; ++c) tot += hist[c][tid];
+    counts[blockIdx.x * kRadix + tid] = (uint16_t)tot;
+}
+
+// Stable scatter of one tile by byte shift / 8; with order set (the last
+// pass) each key's rank goes to order[id] instead.
+template <typename V, typename K, bool kFirst, int kIt>
+__global__ __launch_bounds__(kShortThreads) void k_short_scatter(const void *__restrict__ src,
+                                                                 const uint32_t *__restrict__ src_ids, int n,
+                                                                 int shift, const uint16_t *__restrict__ counts,
+                                                                 int ntiles, K *__restrict__ dst_keys,
+                                                                 uint32_t *__restrict__ dst_ids,
+                                                                 int32_t *__restrict__ order, const int64_t *foff,
+                                                                 int nfields)
+{
+    constexpr int kW = kShortThreads / kWave;
+    constexpr int kGroups = kShortThreads / (kRadix / 2);  // a thread sums two digits over every kGroups-th tile
+    __shared__ uint32_t whist[kW][kRadix];
+    __shared__ uint32_t gbase[kRadix];
+    __shared__ union {
+        struct {
+            uint32_t all[kGroups][kRadix], before[kGroups][kRadix];
+        } sum;
+        Staging<K, uint32_t, kShortThreads, kIt> S;
+    } U;
+    auto &S = U.S;
+    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
+    const int tile = blockIdx.x, t0 = tile * short_tile(kIt);
+    const int count = n - t0 < short_tile(kIt) ? n - t0 : short_tile(kIt);
+    const int first = wave * (kIt * kWave) + lane;
+    using R = SrcT<V, K, kFirst>;
+    R raw[kIt];
+    uint32_t id[kIt];
+#pragma unroll
+    for (int k = 0; k < kIt; ++k) {
+        const int li = first + k * kWave, at = t0 + (li < count ? li : count - 1);
+        raw[k] = ((const R *)src)[at];
+        id[k] = kFirst ? (uint32_t)at : src_ids[at];
+    }
+    // the digits' totals over all tiles and over the tiles before this one
+    {
+        const int g = tid / (kRadix / 2), d = 2 * (tid % (kRadix / 2));
+        uint32_t all0 = 0, all1 = 0, bef0 = 0, bef1 = 0;
+#pragma unroll 16
+        for (int t = g; t < ntiles; t += kGroups) {
+            const uint32_t c = *(const uint32_t *)&counts[t * kRadix + d];
+            all0 += c & 0xffffu;
+            all1 += c >> 16;
+            bef0 += t < tile ? c & 0xffffu : 0u;
+            bef1 += t < tile ? c >> 16 : 0u;
+        }
+        U.sum.all[g][d] = all0;
+        U.sum.all[g][d + 1] = all1;
+        U.sum.before[g][d] = bef0;
+        U.sum.before[g][d + 1] = bef1;
+    }
+    for (int i = tid; i < kW * kRadix; i += kShortThreads) (&whist[0][0])[i] = 0;
+    __syncthreads();
+    uint32_t all = 0, before = 0;
+    if (tid < kRadix) {
+#pragma unroll
+        for (int g = 0; g < kGroups; ++g) {
+            all += U.sum.all[g][tid];
+            before += U.sum.before[g][tid];
+        }
+    }
+    uint32_t total;
+    const uint32_t goff = block_exclusive_scan<uint32_t, kShortThreads>(all, &total) + before;  // (barriers inside)
+    zero_masks(S);
+    __syncthreads();
+    K key[kIt];
+    uint32_t rank[kIt];
+#pragma unroll
+    for (int k = 0; k < kIt; ++k) {
+        const int li = first + k * kWave;
+        if constexpr (kFirst) {
+            bool nan;
+            key[k] = short_key<V, K>(raw[k], id[k], foff, nfields, nan);
+        } else {
+            key[k] = raw[k];
+        }
+        rank[k] = wave_rank<true>((uint32_t)(key[k] >> shift) & (kRadix - 1), li < count, whist[wave], S.mk[wave]);
+    }
+    __syncthreads();
+    const uint32_t start = block_exclusive_scan<uint32_t, kShortThreads>(wave_prefix<kShortThreads>(whist), &total);
+    if (tid < kRadix) {
+        // as in k_scatter: whist the tile position of each wave's first item
+        // of a digit, gbase the global position less the tile position
+        if (!order) {
+#pragma unroll
+            for (int w = 0; w < kW; ++w) whist[w][tid] += start;
+            gbase[tid] = goff - start;
+        } else {
+            gbase[tid] = goff;
+        }
+    }
+    __syncthreads();
+    if (order) {
+#pragma unroll
+        for (int k = 0; k < kIt; ++k) {
+            if (first + k * kWave < count) {
+                const uint32_t d = (uint32_t)(key[k] >> shift) & (kRadix - 1);
+                order[id[k]] = short_rank<V, K>(gbase[d] + whist[wave][d] + rank[k], key[k], foff);
+            }
+        }
+        return;
+    }
+#pragma unroll
+    for (int k = 0; k < kIt; ++k) {
+        if (first + k * kWave < count) {
+            const uint32_t d = (uint32_t)(key[k] >> shift) & (kRadix - 1);
+            stage_put(S, whist[wave][d] + rank[k], key[k], id[k]);
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kIt; ++j) {
+        const int p = tid + j * kShortThreads;
+        if (p < count) {
+            K kk;
+            uint32_t who;
+            stage_get(S, p, kk, who);
+            const uint32_t g = gbase[(uint32_t)(kk >> shift) & (kRadix - 1)] + (uint32_t)p;
+            if (g < (uint32_t)n) {
+                dst_keys[g] = kk;
+                dst_ids[g] = who;
+            }
+        }
+    }
+}
+
 struct OrderLayout {
     size_t keys0, keys1, ids0, ids1, counts, partials, fill, total;
 };
@@ -857,6 +1144,50 @@ __global__ void k_zero_words(uint32_t *__restrict__ w, int64_t nw)
 // passes - 1 value passes, then the last pass orders by the field of each id.
 // Keys are stored stripped of consumed bytes (NoKey) except for batches
 // with 64-bit keys.
+template <typename V, typename K, int kIt>
+int run_order_short(const void *values, int64_t n, int passes, int32_t *order, char *ws, uint32_t *flags,
+                    const int64_t *foff, int nfields, hipStream_t s)
+{
+    const OrderLayout L = order_layout<K>(n);
+    K *keys[2] = {(K *)(ws + L.keys0), (K *)(ws + L.keys1)};
+    uint32_t *ids[2] = {(uint32_t *)(ws + L.ids0), (uint32_t *)(ws + L.ids1)};
+    uint16_t *counts = (uint16_t *)(ws + L.counts);
+    const dim3 grid((unsigned)((n + short_tile(kIt) - 1) / short_tile(kIt))), block(kShortThreads);
+    for (int p = 0; p < passes; ++p) {
+        int32_t *out = p == passes - 1 ? order : nullptr;
+        K *dk = keys[p & 1];
+        uint32_t *di = ids[p & 1];
+        if (p == 0) {
+            hipLaunchKernelGGL((k_short_hist<V, K, true, kIt>), grid, block, 0, s, values, (int)n, 0, counts, flags,
+                               foff, nfields);
+            hipLaunchKernelGGL((k_short_scatter<V, K, true, kIt>), grid, block, 0, s, values,
+                               (const uint32_t *)nullptr, (int)n, 0, counts, (int)grid.x, dk, di, out, foff, nfields);
+        } else {
+            const void *sk = keys[(p - 1) & 1];
+            hipLaunchKernelGGL((k_short_hist<K, K, false, kIt>), grid, block, 0, s, sk, (int)n, 8 * p, counts, flags,
+                               foff, nfields);
+            hipLaunchKernelGGL((k_short_scatter<V, K, false, kIt>), grid, block, 0, s, sk, ids[(p - 1) & 1], (int)n,
+                               8 * p, counts, (int)grid.x, dk, di, out, foff, nfields);
+        }
+    }
+    return launch_status();
+}
+
+// n <= kShortKeys.
+template <typename V, typename K>
+int run_order_few(const void *values, int64_t n, int passes, int32_t *order, char *ws, uint32_t *flags,
+                  const int64_t *foff, int nfields, hipStream_t s)
+{
+    if (n <= kBlockKeys) {
+        hipLaunchKernelGGL((k_order_block<V, K>), dim3(1), dim3(kBlockThreads), 0, s, (const V *)values, (int)n,
+                           passes, order, flags, foff, nfields);
+        return launch_status();
+    }
+    if (n <= short_keys(4)) return run_order_short<V, K, 4>(values, n, passes, order, ws, flags, foff, nfields, s);
+    if (n <= short_keys(8)) return run_order_short<V, K, 8>(values, n, passes, order, ws, flags, foff, nfields, s);
+    return run_order_short<V, K, 16>(values, n, passes, order, ws, flags, foff, nfields, s);
+}
+
 template <typename V, typename K>
 int run_order(const void *values, int64_t n, int passes, int32_t *order, char *ws, uint32_t *flags,
               const int64_t *foff, int nfields, hipStream_t s, bool field_last = false)
@@ -941,6 +1272,8 @@ int launch_rank_u64(const uint64_t *keys, int64_t n, int32_t *rank, char *ws, ui
                     hipStream_t s)
 {
     if (n == 0) return DMS_OK;
+    if (n <= kShortKeys)
+        return run_order_few<uint64_t, uint64_t>(keys, n, 8, rank, ws, flags, nullptr, 0, s);
     return run_order<uint64_t, uint64_t>(keys, n, 8, rank, ws, flags, nullptr, 0, s);
 }
 
@@ -950,6 +1283,8 @@ int launch_order_batch(const float *values, int64_t n, const int64_t *foff, int 
                        int32_t *order, char *ws, uint32_t *flags, hipStream_t s)
 {
     if (n == 0) return DMS_OK;
+    if (n <= kShortKeys)
+        return run_order_few<float, uint64_t>(values, n, batch_passes(nfields), order, ws, flags, foff, nfields, s);
     if (nfields <= kFieldPassFields)  // four value passes, then one field pass
         return run_order<float, uint32_t>(values, n, 5, order, ws, flags, foff, nfields, s, true);
     return run_order<float, uint64_t>(values, n, batch_passes(nfields), order, ws, flags, foff, nfields, s);
@@ -975,6 +1310,11 @@ extern "C" int dms_order(const void *values, int dtype, int64_t n, int32_t *orde
     if (!workspace || workspace_bytes < dms_order_workspace_size(n, dtype)) return DMS_E_WORKSPACE;
     if (const int dc = dms::device_check()) return dc;
     hipStream_t s = (hipStream_t)stream;
+    if (n <= dms::kShortKeys)
+        return dtype == DMS_F32 ? dms::run_order_few<float, uint32_t>(values, n, 4, order, (char *)workspace,
+                                                                      dev_flags, nullptr, 0, s)
+                                : dms::run_order_few<double, uint64_t>(values, n, 8, order, (char *)workspace,
+                                                                       dev_flags, nullptr, 0, s);
     if (dtype == DMS_F32)
         return dms::run_order<float, uint32_t>(values, n, 4, order, (char *)workspace, dev_flags,
                                                nullptr, 0, s);

@@ -8,8 +8,10 @@
 //   jump   pointer doubling until every vertex points at its minimum;
 //   trip   per critical edge: the indices (in the critical-vertex list) of
 //          its two minima and its key -- the order of its higher vertex, then
-//          of its lower one (Section 2.1); an edge whose minima coincide gets
-//          the largest key and is not counted;
+//          of its lower one (Section 2.1), the latter as its rank among the
+//          higher vertex's neighbours (36 bits: five passes instead of the
+//          eight of two orders); an edge whose minima coincide gets the
+//          largest key and is not counted;
 //   sort   ranks of the keys by the radix passes, then placement.
 // The union-find of Algorithm 1 stays on the host (dms_d0_pairs_sorted_host):
 // it is sequential and touches only the minima.
@@ -71,6 +73,9 @@ __global__ __launch_bounds__(kThreads) void k_d0_minima(const int64_t *__restric
     min_order[i] = order[v];
 }
 
+constexpr int kEdgeKeyBits = 36;
+constexpr uint64_t kNoKey = (1ull << kEdgeKeyBits) - 1ull;
+
 __global__ __launch_bounds__(kThreads) void k_d0_trip(const int64_t *__restrict__ crit1, int64_t n1,
                                                       const int32_t *__restrict__ root,
                                                       const int32_t *__restrict__ minidx,
@@ -85,7 +90,7 @@ __global__ __launch_bounds__(kThreads) void k_d0_trip(const int64_t *__restrict_
         const int64_t a = crit1[s] >> 8;
         const int e = (int)(crit1[s] & 255);
         int32_t t0 = -1, t1 = -1;
-        uint64_t k = ~0ull;
+        uint64_t k = kNoKey;
         if (e < 14 && in_grid(a, n) && in_grid(a + st.s[e], n)) {
             const int64_t b = a + st.s[e];
             const int32_t r0 = root[a], r1 = root[b];
@@ -95,7 +100,12 @@ __global__ __launch_bounds__(kThreads) void k_d0_trip(const int64_t *__restrict_
                 atomicOr(flags, (uint32_t)DMS_FLAG_CAPACITY);  // a minimum missing from crit0
             } else if (t0 != t1) {
                 valid = true;
-                k = ((uint64_t)(uint32_t)order[a] << 32) | (uint32_t)order[b];
+                const uint32_t ob = (uint32_t)order[b];
+                uint32_t r = 0;
+#pragma unroll
+                for (int j = 0; j < 14; ++j)
+                    if (in_grid(a + st.s[j], n)) r += (uint32_t)order[a + st.s[j]] < ob ? 1u : 0u;
+                k = (uint64_t)(uint32_t)order[a] << 4 | r;
             }
         } else {
             atomicOr(flags, (uint32_t)DMS_FLAG_CAPACITY);
@@ -208,7 +218,7 @@ extern "C" int dms_d0_triplets(const uint32_t *rec, const int32_t *order, const 
     if (n1 > 0) {
         hipLaunchKernelGGL(k_d0_trip, dim3(blocks_for(n1)), dim3(kThreads), 0, s, crit1, n1, roots, minidx,
                            order, n, st, key, m0, m1, count, dev_flags);
-        const int st2 = launch_rank_u64(key, n1, rank, ws + L.rws, rflags, s);
+        const int st2 = launch_rank_u64(key, n1, kEdgeKeyBits, rank, ws + L.rws, rflags, s);
         if (st2) return st2;
         hipLaunchKernelGGL(k_d0_place, dim3(blocks_for(n1)), dim3(kThreads), 0, s, rank, n1, crit1, m0, m1,
                            tri_edge, tri_min0, tri_min1);

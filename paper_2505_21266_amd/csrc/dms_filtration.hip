@@ -2,11 +2,13 @@
 // order of Section 2.1: a cell's key is the list of its vertex orders sorted
 // decreasingly, and keys of one dimension compare lexicographically.
 //
-// A key holds at most four orders, each below 2^31.  It is packed into two
-// 64-bit words, hi = o1 << 32 | o2 and lo = o3 << 32 | o4 (absent entries
-// 0), and the list is ranked by the radix passes: by lo first, then stably by
-// hi, which is the lexicographic order of (hi, lo).  Vertices and edges need
-// the hi word only.
+// Two cells compare by their highest vertices' orders unless they share that
+// vertex w; then their other vertices are neighbours of w, and their orders
+// compare like their ranks among w's (at most 14) neighbours.  So the key is
+// the order of w (32 bits) above the ranks of the other vertices, decreasing,
+// 4 bits each: at most 44 bits, ranked by one radix sort of 4 to 6 passes
+// (two 64-bit words of plain orders took 8 passes for vertices and edges and
+// 16 for triangles and tets).
 #include "dms_common.hpp"
 #include "dms_internal.hpp"
 #include "dms_tables.hpp"
@@ -36,12 +38,8 @@ Geom make_geom()
     return g;
 }
 
-__device__ __forceinline__ void cswap_desc(uint32_t &a, uint32_t &b)
-{
-    const uint32_t hi = max(a, b), lo = min(a, b);
-    a = hi;
-    b = lo;
-}
+// Bits of a dimension's keys.
+constexpr int key_bits(int dim) { return 32 + 4 * dim; }
 
 // Keys of the cells: code = (maxv << 8) | local index (0 for a vertex,
 // neighbour e for an edge, star triangle t, star tet q).  A code naming no
@@ -49,8 +47,7 @@ __device__ __forceinline__ void cswap_desc(uint32_t &a, uint32_t &b)
 __global__ __launch_bounds__(kThreads) void k_cell_keys(const int64_t *__restrict__ codes, int64_t count,
                                                         int dim, const int32_t *__restrict__ order,
                                                         int64_t nx, int64_t ny, int64_t nz, Geom g,
-                                                        uint64_t *__restrict__ hi, uint64_t *__restrict__ lo,
-                                                        uint32_t *flags)
+                                                        uint64_t *__restrict__ key, uint32_t *flags)
 {
     const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     if (i >= count) return;
@@ -78,65 +75,71 @@ __global__ __launch_bounds__(kThreads) void k_cell_keys(const int64_t *__restric
         oth[2] = g.tet[q][2];
     }
     uint32_t o[4] = {0u, 0u, 0u, 0u};
+    uint64_t k = 0;
     if (!bad) {
         const int64_t x = v % nx, y = (v / nx) % ny, z = v / (nx * ny);
+        int64_t tx = x, ty = y, tz = z;  // the highest vertex
         o[0] = (uint32_t)order[v];
-        for (int k = 0; k < dim; ++k) {
-            const int e = oth[k];
-            const int64_t a = x + g.nb[e][0], b = y + g.nb[e][1], c = z + g.nb[e][2];
-            if (a < 0 || b < 0 || c < 0 || a >= nx || b >= ny || c >= nz) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            if (c >= dim) continue;
+            const int e = oth[c];
+            const int64_t a = x + g.nb[e][0], b = y + g.nb[e][1], d = z + g.nb[e][2];
+            if (a < 0 || b < 0 || d < 0 || a >= nx || b >= ny || d >= nz) {
                 bad = true;
-                break;
+                continue;
             }
-            o[k + 1] = (uint32_t)order[a + nx * (b + ny * c)];
+            o[c + 1] = (uint32_t)order[a + nx * (b + ny * d)];
+            if (o[c + 1] > o[0]) {  // (not so for codes as the extraction writes them)
+                const uint32_t s = o[0];
+                o[0] = o[c + 1];
+                o[c + 1] = s;
+                tx = a;
+                ty = b;
+                tz = d;
+            }
         }
+        // ranks of the other vertices among the highest one's neighbours
+        uint32_t r[3] = {0u, 0u, 0u};
+        if (!bad && dim > 0) {
+#pragma unroll
+            for (int e = 0; e < 14; ++e) {
+                const int64_t a = tx + g.nb[e][0], b = ty + g.nb[e][1], d = tz + g.nb[e][2];
+                if (a < 0 || b < 0 || d < 0 || a >= nx || b >= ny || d >= nz) continue;
+                const uint32_t w = (uint32_t)order[a + nx * (b + ny * d)];
+#pragma unroll
+                for (int c = 0; c < 3; ++c) r[c] += w < o[c + 1] ? 1u : 0u;
+            }
+        }
+        // decreasing; the absent ones (0) stay last
+        uint32_t hi = r[0] > r[1] ? r[0] : r[1], mid = r[0] > r[1] ? r[1] : r[0], low = r[2];
+        if (dim == 3) {
+            if (low > mid) { const uint32_t s = mid; mid = low; low = s; }
+            if (mid > hi) { const uint32_t s = hi; hi = mid; mid = s; }
+        }
+        const uint32_t local = dim == 0 ? 0u : dim == 1 ? hi : dim == 2 ? hi << 4 | mid : hi << 8 | mid << 4 | low;
+        k = (uint64_t)o[0] << (4 * dim) | local;
     }
-    // decreasing: a five-comparator network on four entries; the absent ones
-    // (0) end up last, where every cell of the dimension has them
-    cswap_desc(o[0], o[1]);
-    cswap_desc(o[2], o[3]);
-    cswap_desc(o[0], o[2]);
-    cswap_desc(o[1], o[3]);
-    cswap_desc(o[1], o[2]);
     if (bad) {
         atomicOr(flags, (uint32_t)DMS_FLAG_BADCODE);
-        hi[i] = ~0ull;
-        lo[i] = ~0ull;
-        return;
+        k = (1ull << key_bits(dim)) - 1ull;
     }
-    hi[i] = ((uint64_t)o[0] << 32) | o[1];
-    lo[i] = ((uint64_t)o[2] << 32) | o[3];
+    key[i] = k;
 }
 
-// out[rank[i]] = in[i] for the codes, and (optionally) the keys.
+// out_codes[rank[i]] = in_codes[i].
 __global__ __launch_bounds__(kThreads) void k_cell_place(const int32_t *__restrict__ rank, int64_t count,
                                                          const int64_t *__restrict__ in_codes,
-                                                         const uint64_t *__restrict__ in_key,
-                                                         int64_t *__restrict__ out_codes,
-                                                         uint64_t *__restrict__ out_key)
+                                                         int64_t *__restrict__ out_codes)
 {
     const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     if (i >= count) return;
     const int32_t r = rank[i];
-    if (r < 0 || r >= count) return;
-    if (out_codes) out_codes[r] = in_codes[i];
-    if (out_key) out_key[r] = in_key[i];
-}
-
-// rank[i] = second[first[i]]: the position after the low-word pass, then
-// after the high-word pass.
-__global__ __launch_bounds__(kThreads) void k_compose(const int32_t *__restrict__ first,
-                                                      const int32_t *__restrict__ second, int64_t count,
-                                                      int32_t *__restrict__ rank)
-{
-    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (i >= count) return;
-    const int32_t a = first[i];
-    rank[i] = a >= 0 && a < count ? second[a] : a;
+    if (r >= 0 && r < count) out_codes[r] = in_codes[i];
 }
 
 struct RankLayout {
-    size_t hi, lo, hi2, r1, r2, rws, total;
+    size_t key, rws, total;
 };
 
 RankLayout rank_layout(int64_t count)
@@ -144,11 +147,7 @@ RankLayout rank_layout(int64_t count)
     const size_t c = (size_t)(count > 0 ? count : 1);
     RankLayout L{};
     size_t off = 0;
-    L.hi = off; off += align_up(c * 8, 256);
-    L.lo = off; off += align_up(c * 8, 256);
-    L.hi2 = off; off += align_up(c * 8, 256);
-    L.r1 = off; off += align_up(c * 4, 256);
-    L.r2 = off; off += align_up(c * 4, 256);
+    L.key = off; off += align_up(c * 8, 256);
     L.rws = off; off += rank_u64_workspace_size(count);
     L.total = off;
     return L;
@@ -165,22 +164,10 @@ int launch_cell_ranks(const int64_t *codes, int64_t count, int dim, const int32_
 {
     if (count == 0) return DMS_OK;
     const RankLayout L = rank_layout(count);
-    uint64_t *hi = (uint64_t *)(ws + L.hi), *lo = (uint64_t *)(ws + L.lo), *hi2 = (uint64_t *)(ws + L.hi2);
-    int32_t *r1 = (int32_t *)(ws + L.r1), *r2 = (int32_t *)(ws + L.r2);
-    const unsigned blocks = blocks_for(count);
-    hipLaunchKernelGGL(k_cell_keys, dim3(blocks), dim3(kThreads), 0, s, codes, count, dim, order, dims[0],
-                       dims[1], dims[2], make_geom(), hi, lo, flags);
-    if (dim < 2) return launch_rank_u64(hi, count, rank, ws + L.rws, flags, s);
-    // the low word first; the high word's stable ranking then orders by
-    // (hi, lo)
-    int st = launch_rank_u64(lo, count, r1, ws + L.rws, flags, s);
-    if (st) return st;
-    hipLaunchKernelGGL(k_cell_place, dim3(blocks), dim3(kThreads), 0, s, r1, count, (const int64_t *)nullptr,
-                       hi, (int64_t *)nullptr, hi2);
-    st = launch_rank_u64(hi2, count, r2, ws + L.rws, flags, s);
-    if (st) return st;
-    hipLaunchKernelGGL(k_compose, dim3(blocks), dim3(kThreads), 0, s, r1, r2, count, rank);
-    return launch_status();
+    uint64_t *key = (uint64_t *)(ws + L.key);
+    hipLaunchKernelGGL(k_cell_keys, dim3(blocks_for(count)), dim3(kThreads), 0, s, codes, count, dim, order, dims[0],
+                       dims[1], dims[2], make_geom(), key, flags);
+    return launch_rank_u64(key, count, key_bits(dim), rank, ws + L.rws, flags, s);
 }
 
 }  // namespace dms
@@ -218,6 +205,6 @@ extern "C" int dms_critical_sort(const int64_t *codes, int64_t count, int dim, c
                                      dev_flags, s);
     if (st) return st;
     hipLaunchKernelGGL(k_cell_place, dim3(blocks_for(count)), dim3(kThreads), 0, s, rank, count, codes,
-                       (const uint64_t *)nullptr, sorted, (uint64_t *)nullptr);
+                       sorted);
     return launch_status();
 }

@@ -36,10 +36,10 @@ int launch_gradient_batch(int variant, const int32_t *order, const BatchField *f
                           const int64_t *tile_start, const uint16_t *tile_field, int64_t total_tiles,
                           int64_t total_verts, uint32_t *rec, uint32_t *mark, char *ws, hipStream_t s);
 
-// Ranks of n 64-bit unsigned keys (rank[i] = position of key i in the
-// ascending stable sort), with the order passes.
+// Ranks of n unsigned keys below 2^bits (rank[i] = position of key i in the
+// ascending stable sort), with the order passes: one for every 8 bits.
 size_t rank_u64_workspace_size(int64_t n);
-int launch_rank_u64(const uint64_t *keys, int64_t n, int32_t *rank, char *ws, uint32_t *flags,
+int launch_rank_u64(const uint64_t *keys, int64_t n, int bits, int32_t *rank, char *ws, uint32_t *flags,
                     hipStream_t s);
 
 // Batched order: values of all fields concatenated (float32); the field of

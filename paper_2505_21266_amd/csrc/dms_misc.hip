@@ -14,8 +14,9 @@ namespace {
 // of its two simplices, so their derivatives with respect to the field are
 // indicator vectors at the max vertices (code >> 8).  The 2 npairs
 // contributions (births c < npairs, deaths c = npairs + p) are keyed by
-// their target vertex (targets outside [0, n) get the largest key and are
-// dropped), ranked by a stable sort, and each run of equal target is summed
+// their target vertex (targets outside [0, n) get the largest key, n, and are
+// dropped), of which only the bits of n are sorted (3 passes instead of 8 for
+// 128^3 vertices), ranked by a stable sort, and each run of equal target is summed
 // by its first element in contribution order: every vertex gets the same
 // sum, in the same order, on every run.
 __global__ void k_backward_keys(const int64_t *__restrict__ bcode, const int64_t *__restrict__ dcode,
@@ -24,7 +25,7 @@ __global__ void k_backward_keys(const int64_t *__restrict__ bcode, const int64_t
     const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= 2 * npairs) return;
     const int64_t v = (c < npairs ? bcode[c] : dcode[c - npairs]) >> 8;
-    key[c] = v >= 0 && v < n ? (uint64_t)v : ~0ull;
+    key[c] = v >= 0 && v < n ? (uint64_t)v : (uint64_t)n;
 }
 
 __global__ void k_backward_place(const int32_t *__restrict__ rank, int64_t m, int32_t *__restrict__ at)
@@ -34,13 +35,13 @@ __global__ void k_backward_place(const int32_t *__restrict__ rank, int64_t m, in
 }
 
 __global__ void k_backward_sum(const int32_t *__restrict__ at, const uint64_t *__restrict__ key, int64_t m,
-                               int64_t npairs, const double *__restrict__ gb, const double *__restrict__ gd,
-                               double *__restrict__ grad)
+                               int64_t npairs, int64_t n, const double *__restrict__ gb,
+                               const double *__restrict__ gd, double *__restrict__ grad)
 {
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= m) return;
     const uint64_t v = key[at[j]];
-    if (v == ~0ull || (j > 0 && key[at[j - 1]] == v)) return;
+    if (v == (uint64_t)n || (j > 0 && key[at[j - 1]] == v)) return;
     double s = 0.0;
     for (int64_t q = j; q < m && key[at[q]] == v; ++q) {
         const int64_t c = at[q];
@@ -193,10 +194,12 @@ extern "C" int dms_gradient_backward(const int64_t *birth_code, const int64_t *d
         int32_t *rank = (int32_t *)(ws + L.rank), *at = (int32_t *)(ws + L.at);
         hipLaunchKernelGGL(k_backward_keys, dim3(blocks_of(m)), dim3(256), 0, s, birth_code, death_code,
                            npairs, n, key);
-        const int st = launch_rank_u64(key, m, rank, ws + L.rws, (uint32_t *)(ws + L.flags), s);
+        int bits = 1;
+        while (bits < 63 && (n >> bits) != 0) ++bits;
+        const int st = launch_rank_u64(key, m, bits, rank, ws + L.rws, (uint32_t *)(ws + L.flags), s);
         if (st) return st;
         hipLaunchKernelGGL(k_backward_place, dim3(blocks_of(m)), dim3(256), 0, s, rank, m, at);
-        hipLaunchKernelGGL(k_backward_sum, dim3(blocks_of(m)), dim3(256), 0, s, at, key, m, npairs, g_birth,
+        hipLaunchKernelGGL(k_backward_sum, dim3(blocks_of(m)), dim3(256), 0, s, at, key, m, npairs, n, g_birth,
                            g_death, grad);
     }
     return launch_status();

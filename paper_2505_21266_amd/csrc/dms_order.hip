@@ -1103,6 +1103,19 @@ void radix_pass(const PassArgs &A)
                        A.n, A.shift, A.strip, A.counts, nt, A.dkeys, A.dids, A.foff, A.nfields);
 }
 
+// The first pass of 64-bit keys of which only the low 8 (1 + kd's bits) matter
+// (ranked integers), by the bytes stored after it.
+int radix_first_u64(int kd, const PassArgs &A)
+{
+    switch (kd) {
+    case 8: radix_pass<uint64_t, uint64_t, uint64_t, true>(A); return DMS_OK;
+    case 4: radix_pass<uint64_t, uint64_t, uint32_t, true>(A); return DMS_OK;
+    case 2: radix_pass<uint64_t, uint64_t, uint16_t, true>(A); return DMS_OK;
+    case 1: radix_pass<uint64_t, uint64_t, uint8_t, true>(A); return DMS_OK;
+    default: return DMS_E_ARG;
+    }
+}
+
 // A middle pass by the stored key's bytes before (ks) and after (kd) it.
 int radix_mid_pass(int ks, int kd, const PassArgs &A)
 {
@@ -1213,9 +1226,13 @@ int run_order(const void *values, int64_t n, int passes, int32_t *order, char *w
             PassArgs A{src, sids, n, shift, strip ? 8 : 0, counts, partials, flags, keys[p & 1], ids[p & 1],
                        foff, nfields, s};
             if (p == 0) {
-                // the first pass writes K: at least 24 bits of a 32-bit key and 56 of a 64-bit one remain
-                if (strip && key_bytes(key_bits - 8) != (int)sizeof(K)) return DMS_E_ARG;
-                radix_pass<V, K, K, true>(A);
+                // the first pass over values writes K: 24 bits of a 32-bit key and 56 of a 64-bit one remain
+                if constexpr (std::is_same_v<V, uint64_t>) {
+                    if (const int st = radix_first_u64(key_bytes(key_bits - 8), A)) return st;
+                } else {
+                    if (strip && key_bytes(key_bits - 8) != (int)sizeof(K)) return DMS_E_ARG;
+                    radix_pass<V, K, K, true>(A);
+                }
             } else {
                 const int ks = strip ? key_bytes(key_bits - 8 * p) : (int)sizeof(K);
                 const int kd = strip ? key_bytes(key_bits - 8 * (p + 1)) : (int)sizeof(K);
@@ -1268,13 +1285,14 @@ int run_order(const void *values, int64_t n, int passes, int32_t *order, char *w
 
 size_t rank_u64_workspace_size(int64_t n) { return order_layout<uint64_t>(n > 0 ? n : 1).total; }
 
-int launch_rank_u64(const uint64_t *keys, int64_t n, int32_t *rank, char *ws, uint32_t *flags,
+int launch_rank_u64(const uint64_t *keys, int64_t n, int bits, int32_t *rank, char *ws, uint32_t *flags,
                     hipStream_t s)
 {
     if (n == 0) return DMS_OK;
+    const int passes = bits <= 16 ? 2 : (bits + 7) / 8;
     if (n <= kShortKeys)
-        return run_order_few<uint64_t, uint64_t>(keys, n, 8, rank, ws, flags, nullptr, 0, s);
-    return run_order<uint64_t, uint64_t>(keys, n, 8, rank, ws, flags, nullptr, 0, s);
+        return run_order_few<uint64_t, uint64_t>(keys, n, passes, rank, ws, flags, nullptr, 0, s);
+    return run_order<uint64_t, uint64_t>(keys, n, passes, rank, ws, flags, nullptr, 0, s);
 }
 
 size_t order_batch_workspace_size(int64_t n) { return order_layout<uint64_t>(n > 0 ? n : 1).total; }

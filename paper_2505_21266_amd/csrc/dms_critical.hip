@@ -728,21 +728,6 @@ __global__ __launch_bounds__(kThreads) void k_crit_fill_masked(
     }
 }
 
-__global__ void k_crit_finish(const uint64_t *offs, int64_t ntiles, int64_t *counts, int64_t cap0,
-                              int64_t cap1, int64_t cap2, int64_t cap3, uint32_t *flags)
-{
-    if (threadIdx.x != 0) return;
-    const int64_t cap[4] = {cap0, cap1, cap2, cap3};
-    bool over = false;
-    for (int d = 0; d < 4; ++d) {
-        const int64_t tot = (int64_t)(offs[(int64_t)(d + 1) * ntiles] - offs[(int64_t)d * ntiles]);
-        counts[d] = tot;
-        over = over || tot > cap[d];
-    }
-    if (over) atomicOr(flags, (uint32_t)DMS_FLAG_CAPACITY);
-}
-
-
 // Batched fill from the critical mask: records of whole fields
 // concatenated; codes carry the field-local vertex id.  A wave takes
 // kTilesPerWave consecutive tiles (one mask word per lane) and their flagged
@@ -850,6 +835,172 @@ __global__ void k_crit_finish_batch(const uint64_t *offs, int64_t ntiles, int nf
     }
 }
 
+// ---------------------------------------------------------------------------
+// Short boxes (at most kShortTiles tiles).  One wave per two tiles, as above,
+// leaves most of the chip idle and each wave with a long chain of chunks (a
+// 24 x 20 x 16 noise field: 17 us to count and 59 us to fill, on four waves).
+// Here a tile is counted by a block, its kGroups groups of kGroupRecs records
+// are filled by a wave each, and one block scans the tile counts and sets the
+// list counts.  Without a mask every record is read.
+constexpr int64_t kShortTiles = 4096;
+constexpr int kGroups = 8;
+constexpr int kGroupRecs = kTileRecs / kGroups;
+constexpr int kGroupWords = kGroupRecs / 32;
+static_assert(kGroups * sizeof(uint64_t) <= kCand * sizeof(uint16_t), "group counts in the candidates' space");
+
+// Counts a tile: groups[tile * kGroups + g] = packed counts of the tile's
+// groups before g.
+__global__ __launch_bounds__(kThreads) void k_short_count(const uint4 *__restrict__ rec,
+                                                          const uint32_t *__restrict__ mask, int64_t nbox,
+                                                          uint64_t *__restrict__ tile_counts, int64_t ntiles,
+                                                          uint64_t *__restrict__ groups)
+{
+    __shared__ uint64_t gsum[kGroups];
+    const int tid = threadIdx.x, wave = tid / kWave, lane = lane_id();
+    const int64_t tile = blockIdx.x, w0 = tile * kTileRecs + wave * (kTileRecs / kWavesPerBlock);
+    uint64_t pk[kPerThread];
+#pragma unroll
+    for (int k = 0; k < kPerThread; ++k) {
+        const int64_t r = w0 + k * kWave + lane;
+        uint32_t c[4] = {0, 0, 0, 0};
+        if (r < nbox && (!mask || ((mask[r >> 5] >> (r & 31)) & 1u))) {
+            const uint4 w = rec[r];
+            count_critical((uint64_t)w.x | ((uint64_t)w.y << 32), (uint64_t)w.z | ((uint64_t)w.w << 32), c);
+        }
+        pk[k] = pack4(c);
+    }
+    constexpr int kRows = kGroupRecs / kWave;  // rows of a group, kGroups / kWavesPerBlock groups of a wave
+    static_assert(kRows * (kGroups / kWavesPerBlock) == kPerThread, "a wave's rows");
+#pragma unroll
+    for (int g = 0; g < kGroups / kWavesPerBlock; ++g) {
+        uint64_t sum = 0;
+#pragma unroll
+        for (int k = 0; k < kRows; ++k) sum += pk[g * kRows + k];
+#pragma unroll
+        for (int off = kWave / 2; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+        if (lane == 0) gsum[wave * (kGroups / kWavesPerBlock) + g] = sum;
+    }
+    __syncthreads();
+    if (tid <= kGroups) {
+        uint64_t before = 0;
+#pragma unroll
+        for (int g = 0; g < kGroups; ++g) before += g < tid ? gsum[g] : 0;
+        if (tid < kGroups) {
+            groups[tile * kGroups + tid] = before;
+        } else {
+#pragma unroll
+            for (int d = 0; d < 4; ++d) tile_counts[(int64_t)d * ntiles + tile] = lane16(before, d);
+        }
+    }
+    if (tile == 0 && tid == kWave) tile_counts[4 * ntiles] = 0;
+}
+
+__device__ __forceinline__ void finish_counts(const uint64_t *offs, int64_t ntiles, int64_t *counts, int64_t cap0,
+                                              int64_t cap1, int64_t cap2, int64_t cap3, uint32_t *flags)
+{
+    const int d = threadIdx.x;
+    if (d >= 4) return;
+    const int64_t cap = d == 0 ? cap0 : d == 1 ? cap1 : d == 2 ? cap2 : cap3;
+    const int64_t tot = (int64_t)(offs[(int64_t)(d + 1) * ntiles] - offs[(int64_t)d * ntiles]);
+    counts[d] = tot;
+    if (tot > cap) atomicOr(flags, (uint32_t)DMS_FLAG_CAPACITY);
+}
+
+__global__ void k_crit_finish(const uint64_t *offs, int64_t ntiles, int64_t *counts, int64_t cap0, int64_t cap1,
+                              int64_t cap2, int64_t cap3, uint32_t *flags)
+{
+    finish_counts(offs, ntiles, counts, cap0, cap1, cap2, cap3, flags);
+}
+
+// Exclusive scan of the tile counts by one block, and the list counts
+// (counts may be null).
+constexpr int kShortScan = 1024;
+
+__global__ __launch_bounds__(kShortScan) void k_short_scan(uint64_t *__restrict__ tc, int64_t ntiles, int64_t *counts,
+                                                           int64_t cap0, int64_t cap1, int64_t cap2, int64_t cap3,
+                                                           uint32_t *flags)
+{
+    const int len = (int)(4 * ntiles + 1), per = (len + kShortScan - 1) / kShortScan;
+    const int first = threadIdx.x * per, end = first + per < len ? first + per : len;
+    uint64_t sum = 0;
+    for (int i = first; i < end; ++i) sum += tc[i];
+    uint64_t total;
+    uint64_t run = block_exclusive_scan<uint64_t, kShortScan>(sum, &total);
+    for (int i = first; i < end; ++i) {
+        const uint64_t c = tc[i];
+        tc[i] = run;
+        run += c;
+    }
+    if (!counts) return;
+    __syncthreads();
+    finish_counts(tc, ntiles, counts, cap0, cap1, cap2, cap3, flags);
+}
+
+// Fills the cells of one group a wave, its (flagged) records kWave at a time.
+// foff: offsets of a batch's fields (codes carry the field-local vertex), or
+// null for the box of a single field.
+__global__ __launch_bounds__(kThreads) void k_short_fill(
+    const uint4 *__restrict__ rec, const uint32_t *__restrict__ mask, int64_t nbox,
+    const uint64_t *__restrict__ offs, int64_t ntiles, const uint64_t *__restrict__ groups, int64_t w0, int64_t w1,
+    int64_t lo0, int64_t lo1, int64_t lo2, int64_t nx, int64_t ny, const int64_t *__restrict__ foff, int nfields,
+    int64_t *crit0, int64_t *crit1, int64_t *crit2, int64_t *crit3, int64_t cap0, int64_t cap1, int64_t cap2,
+    int64_t cap3)
+{
+    const DecodeTables &D = g_decode;
+    const int lane = lane_id();
+    const int64_t group =
+        (int64_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * kWavesPerBlock + threadIdx.x / kWave));
+    const int64_t r0 = group * kGroupRecs;
+    if (r0 >= nbox) return;
+    const int64_t tile = group / kGroups;
+    // the group's mask words in the first lanes (all records flagged without a mask)
+    uint32_t word = 0;
+    if (lane < kGroupWords) {
+        const int64_t left = nbox - r0 - 32 * lane;
+        if (left > 0)
+            word = mask ? mask[group * kGroupWords + lane] : left >= 32 ? ~0u : (1u << (uint32_t)left) - 1u;
+    }
+    if (!__ballot(word != 0u)) return;
+    const uint64_t before = groups[group];
+    uint64_t at[4];
+#pragma unroll
+    for (int d = 0; d < 4; ++d)
+        at[d] = offs[(int64_t)d * ntiles + tile] - offs[(int64_t)d * ntiles] + lane16(before, d);
+    int f0 = 0;  // field of the group's first record
+    if (foff)
+        for (int step = 1 << 10; step > 0; step >>= 1)
+            if (f0 + step < nfields && foff[f0 + step] <= r0) f0 += step;
+    uint32_t inc;
+    const uint32_t total = flag_scan(word, lane, inc);
+#pragma unroll 1
+    for (uint32_t c0 = 0; c0 < total; c0 += kWave) {
+        const uint32_t j = c0 + (uint32_t)lane;
+        const bool take = j < total;
+        const int64_t r = r0 + flag_at(word, inc, take ? j : c0);
+        uint64_t pk = 0;
+        uint32_t ce = 0, cq = 0;
+        uint64_t ct = 0;
+        int64_t v = 0;
+        if (take && r < nbox) {
+            const uint4 w = rec[r];
+            pk = decode_record((uint64_t)w.x | ((uint64_t)w.y << 32), (uint64_t)w.z | ((uint64_t)w.w << 32), D,
+                               ce, ct, cq);
+            if (foff) {
+                int f = f0;
+                while (f + 1 < nfields && foff[f + 1] <= r) ++f;
+                v = r - foff[f];
+            } else {
+                v = box_vertex(r, w0, w1, lo0, lo1, lo2, nx, ny);
+            }
+        }
+        if (!__ballot(pk != 0)) continue;
+        const uint64_t tot =
+            emit_codes(ce, ct, cq, v, pk, at, crit0, crit1, crit2, crit3, cap0, cap1, cap2, cap3);
+#pragma unroll
+        for (int d = 0; d < 4; ++d) at[d] += lane16(tot, d);
+    }
+}
+
 __global__ void k_crit_empty(int64_t *counts)
 {
     if (threadIdx.x < 4) counts[threadIdx.x] = 0;
@@ -907,20 +1058,37 @@ int launch_critical(const uint32_t *rec, const uint32_t *mask, const int64_t *di
         hipLaunchKernelGGL(k_crit_empty, dim3(1), dim3(64), 0, s, counts);
         return launch_status();
     }
+    // a call that only counts (no list has room) needs no fill
+    const bool fill = cap[0] > 0 || cap[1] > 0 || cap[2] > 0 || cap[3] > 0;
+    if (ntiles <= kShortTiles) {
+        uint64_t *groups = (uint64_t *)cand;
+        hipLaunchKernelGGL(k_short_count, dim3((unsigned)ntiles), dim3(kThreads), 0, s, (const uint4 *)rec, mask,
+                           nbox, tc, ntiles, groups);
+        hipLaunchKernelGGL(k_short_scan, dim3(1), dim3(kShortScan), 0, s, tc, ntiles, counts, cap[0], cap[1], cap[2],
+                           cap[3], dev_flags);
+        if (fill)
+            hipLaunchKernelGGL(k_short_fill, dim3((unsigned)(ntiles * kGroups / kWavesPerBlock)), dim3(kThreads), 0,
+                               s, (const uint4 *)rec, mask, nbox, tc, ntiles, groups, w0, w1, lo[0], lo[1], lo[2],
+                               dims[0], dims[1], (const int64_t *)nullptr, 0, crit0, crit1, crit2, crit3, cap[0],
+                               cap[1], cap[2], cap[3]);
+        return launch_status();
+    }
     if (mask) {
         const int64_t per_block = (int64_t)kWavesPerBlock * kTilesPerWave;
         const unsigned blocks = (unsigned)((ntiles + per_block - 1) / per_block);
         hipLaunchKernelGGL(k_crit_count_masked, dim3(blocks), dim3(kThreads), 0, s, (const uint4 *)rec, mask,
                            nbox, tc, ntiles);
         exclusive_scan<uint64_t>(tc, len, partials, s);
-        hipLaunchKernelGGL(k_crit_fill_masked, dim3(blocks), dim3(kThreads), 0, s, (const uint4 *)rec, mask,
+        if (fill)
+            hipLaunchKernelGGL(k_crit_fill_masked, dim3(blocks), dim3(kThreads), 0, s, (const uint4 *)rec, mask,
                            nbox, tc, ntiles, w0, w1, lo[0], lo[1], lo[2], dims[0], dims[1], crit0, crit1,
                            crit2, crit3, cap[0], cap[1], cap[2], cap[3]);
     } else {
         hipLaunchKernelGGL(k_crit_count, dim3((unsigned)ntiles), dim3(kThreads), 0, s, (const uint4 *)rec,
                            nbox, tc, ntiles, cand, ncand);
         exclusive_scan<uint64_t>(tc, len, partials, s);
-        hipLaunchKernelGGL(k_crit_fill, dim3((unsigned)ntiles), dim3(kThreads), 0, s, (const uint4 *)rec,
+        if (fill)
+            hipLaunchKernelGGL(k_crit_fill, dim3((unsigned)ntiles), dim3(kThreads), 0, s, (const uint4 *)rec,
                            nbox, tc, ntiles, cand, ncand, w0, w1, lo[0], lo[1], lo[2], dims[0], dims[1],
                            crit0, crit1, crit2, crit3, cap[0], cap[1], cap[2], cap[3]);
     }
@@ -962,13 +1130,29 @@ int launch_critical_batch(const uint32_t *rec, const uint32_t *mask, int64_t n, 
     const CritLayout L = crit_layout(ntiles);
     uint64_t *tc = (uint64_t *)ws;
     uint64_t *partials = (uint64_t *)(ws + L.partials);
-    const int64_t per_block = (int64_t)kWavesPerBlock * kTilesPerWave;
-    const unsigned blocks = (unsigned)((ntiles + per_block - 1) / per_block);
-    hipLaunchKernelGGL(k_crit_count_masked, dim3(blocks), dim3(kThreads), 0, s, (const uint4 *)rec, mask, n, tc,
-                       ntiles);
-    exclusive_scan<uint64_t>(tc, len, partials, s);
-    hipLaunchKernelGGL(k_crit_fill_batch, dim3(blocks), dim3(kThreads), 0, s, (const uint4 *)rec, mask, n, tc,
-                       ntiles, foff, nfields, crit[0], crit[1], crit[2], crit[3], cap[0], cap[1], cap[2], cap[3]);
+    const bool fill = cap[0] > 0 || cap[1] > 0 || cap[2] > 0 || cap[3] > 0;
+    if (ntiles <= kShortTiles) {
+        uint64_t *groups = (uint64_t *)(ws + L.cand);
+        hipLaunchKernelGGL(k_short_count, dim3((unsigned)ntiles), dim3(kThreads), 0, s, (const uint4 *)rec, mask, n,
+                           tc, ntiles, groups);
+        hipLaunchKernelGGL(k_short_scan, dim3(1), dim3(kShortScan), 0, s, tc, ntiles, (int64_t *)nullptr, (int64_t)0,
+                           (int64_t)0, (int64_t)0, (int64_t)0, flags);
+        if (fill)
+            hipLaunchKernelGGL(k_short_fill, dim3((unsigned)(ntiles * kGroups / kWavesPerBlock)), dim3(kThreads), 0,
+                               s, (const uint4 *)rec, mask, n, tc, ntiles, groups, (int64_t)1, (int64_t)1, (int64_t)0,
+                               (int64_t)0, (int64_t)0, (int64_t)1, (int64_t)1, foff, nfields, crit[0], crit[1],
+                               crit[2], crit[3], cap[0], cap[1], cap[2], cap[3]);
+    } else {
+        const int64_t per_block = (int64_t)kWavesPerBlock * kTilesPerWave;
+        const unsigned blocks = (unsigned)((ntiles + per_block - 1) / per_block);
+        hipLaunchKernelGGL(k_crit_count_masked, dim3(blocks), dim3(kThreads), 0, s, (const uint4 *)rec, mask, n, tc,
+                           ntiles);
+        exclusive_scan<uint64_t>(tc, len, partials, s);
+        if (fill)
+            hipLaunchKernelGGL(k_crit_fill_batch, dim3(blocks), dim3(kThreads), 0, s, (const uint4 *)rec, mask, n, tc,
+                               ntiles, foff, nfields, crit[0], crit[1], crit[2], crit[3], cap[0], cap[1], cap[2],
+                               cap[3]);
+    }
     hipLaunchKernelGGL(k_crit_fstart_batch, dim3((unsigned)nfields), dim3(kThreads), 0, s, (const uint4 *)rec,
                        tc, ntiles, foff, nfields, offsets);
     hipLaunchKernelGGL(k_crit_finish_batch, dim3(1), dim3(256), 0, s, tc, ntiles, nfields, offsets,

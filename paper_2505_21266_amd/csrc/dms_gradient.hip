@@ -1071,9 +1071,10 @@ __global__ void k_mark_zero(uint32_t *__restrict__ mark, int64_t words)
     if (i < words) mark[i] = 0u;
 }
 
-// Solves the queued general vertices: block b takes entries
-// [b kQueueChunk, (b+1) kQueueChunk) of the filled part, sorts them by the
-// number of lower neighbours and solves them in full rounds.
+// Solves the queued general vertices: block b takes a chunk of the filled
+// part, sorts it by the number of lower neighbours and solves it in full
+// rounds.  A short queue is cut into chunks of one round, for more blocks (a
+// long one into kQueueChunk entries, whose waves are more even).
 __global__ __launch_bounds__(kThreads, 8) void k_gradient_queue(const uint4 *__restrict__ queue,
                                                                 const uint32_t *qcount, uint32_t qcap,
                                                                 uint4 *__restrict__ rec,
@@ -1084,9 +1085,11 @@ __global__ __launch_bounds__(kThreads, 8) void k_gradient_queue(const uint4 *__r
     __shared__ uint16_t perm[kQueueChunk];
     const int tid = threadIdx.x;
     const uint32_t filled = min(*qcount, qcap);
-    const uint64_t start = (uint64_t)blockIdx.x * kQueueChunk;
+    const uint32_t chunk =
+        filled <= 1024u * kThreads && (uint64_t)filled <= (uint64_t)gridDim.x * kThreads ? kThreads : kQueueChunk;
+    const uint64_t start = (uint64_t)blockIdx.x * chunk;
     if (start >= filled) return;  // uniform
-    const uint32_t cnt = (uint32_t)min<uint64_t>(kQueueChunk, filled - start);
+    const uint32_t cnt = (uint32_t)min<uint64_t>(chunk, filled - start);
     load_tables(T);
     if (tid < kSizeBins) bins[tid] = 0;
     __syncthreads();

@@ -483,7 +483,7 @@ def main():
     ms_step = wall / args.steps * 1e3
     value = owned / (ms_step / 1e3) / 1e9
 
-    # dominant call: dms_discrete_gradient (k_mark_zero + k_queue_reset + k_gradient +
+    # dominant call: dms_discrete_gradient (k_gradient_begin + k_gradient +
     # k_gradient_dense + k_gradient_queue on the same stream; the events bracket exactly these launches)
     stage_bytes = {k: ALG_BYTES[k] * owned for k in ALG_BYTES}
     # the masked extraction reads the mask and the flagged records only
@@ -493,7 +493,7 @@ def main():
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                 "traffic": measured_traffic_gb(),
-                "kernel": "dms_discrete_gradient: k_mark_zero + k_queue_reset + k_gradient<64,16> + "
+                "kernel": "dms_discrete_gradient: k_gradient_begin + k_gradient<64,16> + "
                           "k_gradient_dense<64,16> + k_gradient_queue",
                 "kernel_ms": round(ms[dom], 3)}
     out = {

@@ -930,9 +930,10 @@ __global__ __launch_bounds__(kThreads, 8) void k_gradient_batch(const int32_t *_
                                     tile);
 }
 
-// All vertices of one tile that gradient_tile left, solved in rounds of
-// kThreads, dealt by the number of lower neighbours.  part of parts (1 or 4):
-// the quarter of the tile's positions this block takes.
+// All vertices of one tile that gradient_tile left (whole: all of its
+// vertices), solved in rounds of kThreads, dealt by the number of lower
+// neighbours.  part of parts (1 or 4): the quarter of the tile's positions
+// this block takes.
 struct DenseShared {
     StarTables T;
     uint32_t bins[kSizeBins];
@@ -942,15 +943,15 @@ struct DenseShared {
 
 template <typename Keys, int GX, int GY>
 __device__ __forceinline__ void dense_tile(const void *__restrict__ field, const Box &B, int64_t bx, int64_t by,
-                                           int64_t bz, int part, int parts, uint4 *__restrict__ rec,
-                                           uint32_t *__restrict__ mark, DenseShared &sh,
-                                           typename Keys::H *tile)
+                                           int64_t bz, int part, int parts, bool whole,
+                                           uint4 *__restrict__ rec, uint32_t *flags, uint32_t *__restrict__ mark,
+                                           DenseShared &sh, typename Keys::H *tile)
 {
     using S = Tile<GX, GY>;
     using C = typename Keys::C;
     constexpr int kPer = kTileVerts / kThreads;
     const int tid = tile_thread();
-    stage_halo<Keys, GX, GY>(field, B, bx, by, bz, tid, nullptr, tile);
+    stage_halo<Keys, GX, GY>(field, B, bx, by, bz, tid, flags, tile);
     if (tid < kSizeBins) sh.bins[tid] = 0;
     if (tid < kTileVerts / 32) sh.crit[tid] = 0;
     __syncthreads();
@@ -968,7 +969,7 @@ __device__ __forceinline__ void dense_tile(const void *__restrict__ field, const
         const uint32_t low = lower_mask(o, ox);
         const bool gen = general_vertex(low);
         if (k == 0) skip = skip_tables(in, gen);
-        if (mine && in && (gen || (k > 0 && skip))) {
+        if (mine && in && (gen || whole || (k > 0 && skip))) {
             const uint32_t m = (uint32_t)__popc(low);
             sizes |= (128u | m) << (8 * k);
             atomicAdd(&sh.bins[m], 1u);
@@ -1016,6 +1017,7 @@ __device__ __forceinline__ void dense_tile(const void *__restrict__ field, const
 // to a grid of at most kDenseBlocks blocks.  A list with less than a quarter
 // of a tile per block is dealt in quarter tiles, which repeat only the staging.
 constexpr int kDenseBlocks = 256 * 6;
+constexpr int64_t kWholeTiles = 256;  // launches of at most this many tiles use the dense kernel alone
 
 template <typename Solve>
 __device__ __forceinline__ void dense_walk(const Handoff &H, uint32_t ntiles, Solve solve)
@@ -1033,10 +1035,14 @@ __device__ __forceinline__ void dense_walk(const Handoff &H, uint32_t ntiles, So
     }
 }
 
+// whole (without a list): the kernel does all vertices of all tiles by itself.
+// With few tiles the time is the latency of one tile and of the launches, and
+// a table lookup saves nothing: k_gradient, this kernel and the queue's took
+// 13 + 18 + 20 us on a 24 x 20 x 16 noise field, this kernel alone 20.
 template <typename Keys, int GX, int GY>
 __global__ __launch_bounds__(kThreads, 6) void k_gradient_dense(const void *__restrict__ field, Box B,
-                                                                int64_t bx_count, uint32_t ntiles,
-                                                                uint4 *__restrict__ rec, Handoff H,
+                                                                int64_t bx_count, uint32_t ntiles, bool whole,
+                                                                uint4 *__restrict__ rec, Handoff H, uint32_t *flags,
                                                                 uint32_t *__restrict__ mark)
 {
     __shared__ DenseShared sh;
@@ -1044,14 +1050,15 @@ __global__ __launch_bounds__(kThreads, 6) void k_gradient_dense(const void *__re
     load_tables(sh.T);
     dense_walk(H, ntiles, [&](uint32_t t, int part, int parts) {
         const int64_t bz = t % B.w2, col = t / B.w2, bx = col % bx_count, by = col / bx_count;
-        dense_tile<Keys, GX, GY>(field, B, bx, by, bz, part, parts, rec, mark, sh, tile);
+        dense_tile<Keys, GX, GY>(field, B, bx, by, bz, part, parts, whole, rec, flags, mark, sh, tile);
     });
 }
 
 template <int GX, int GY>
 __global__ __launch_bounds__(kThreads, 6) void k_gradient_dense_batch(const int32_t *__restrict__ order, BatchTiles L,
-                                                                      uint32_t ntiles, uint4 *__restrict__ rec,
-                                                                      Handoff H, uint32_t *__restrict__ mark)
+                                                                      uint32_t ntiles, bool whole,
+                                                                      uint4 *__restrict__ rec, Handoff H,
+                                                                      uint32_t *__restrict__ mark)
 {
     __shared__ DenseShared sh;
     __shared__ int32_t tile[Tile<GX, GY>::kHalo];
@@ -1059,16 +1066,17 @@ __global__ __launch_bounds__(kThreads, 6) void k_gradient_dense_batch(const int3
     dense_walk(H, ntiles, [&](uint32_t t, int part, int parts) {
         int64_t bx, by, bz;
         const Box B = batch_box<GX, GY>(L, t, bx, by, bz);
-        dense_tile<RankKeys, GX, GY>(order + B.rec_off, B, bx, by, bz, part, parts, rec, mark, sh, tile);
+        dense_tile<RankKeys, GX, GY>(order + B.rec_off, B, bx, by, bz, part, parts, whole, rec, nullptr, mark, sh,
+                                     tile);
     });
 }
 
-__global__ void k_queue_reset(uint32_t *counts) { counts[threadIdx.x] = 0; }
-
-__global__ void k_mark_zero(uint32_t *__restrict__ mark, int64_t words)
+// Zeroes the mask and the handoff's two counters (either may be null).
+__global__ void k_gradient_begin(uint32_t *__restrict__ mark, int64_t words, uint32_t *counts)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < words) mark[i] = 0u;
+    if (mark && i < words) mark[i] = 0u;
+    if (counts && i < 2) counts[i] = 0u;
 }
 
 // Solves the queued general vertices: block b takes a chunk of the filled
@@ -1276,8 +1284,8 @@ static int64_t workspace_slots(int64_t owned)
 
 size_t gradient_workspace_size(int64_t owned) { return 256 + (size_t)workspace_slots(owned) * sizeof(uint4); }
 
-// Carves the workspace and resets its counters (all null when ws is null).
-static Handoff handoff_begin(char *ws, int64_t owned, hipStream_t s)
+// Carves the workspace (all null when ws is null).
+static Handoff handoff_carve(char *ws, int64_t owned)
 {
     Handoff H{nullptr, nullptr, nullptr, 0, 0};
     if (!ws) return H;
@@ -1289,8 +1297,16 @@ static Handoff handoff_begin(char *ws, int64_t owned, hipStream_t s)
     H.qcap = (uint32_t)(slots - lslots);
     H.list = (uint32_t *)(H.queue + H.qcap);
     H.lcap = (uint32_t)(lslots < 0x1fffffff ? 4 * lslots : 0x7fffffff);
-    hipLaunchKernelGGL(k_queue_reset, dim3(1), dim3(2), 0, s, H.counts);
     return H;
+}
+
+// Clears the mask of `owned` records and the handoff's counters.
+static void gradient_begin(uint32_t *mark, int64_t owned, const Handoff &H, hipStream_t s)
+{
+    if (!mark && !H.counts) return;
+    const int64_t words = mark ? (owned + 31) / 32 : 2;
+    hipLaunchKernelGGL(k_gradient_begin, dim3((unsigned)((words + kThreads - 1) / kThreads)), dim3(kThreads), 0, s,
+                       mark, words, H.counts);
 }
 
 static void queue_finish(const Handoff &H, uint32_t *rec, uint32_t *mark, hipStream_t s)
@@ -1311,20 +1327,18 @@ static int launch_gradient_keys(const void *field, const int64_t *dims, const in
     const Box B{dims[0], dims[1], dims[2], lo[0], lo[1], lo[2], hi[0] - lo[0], hi[1] - lo[1], hi[2] - lo[2], 0};
     if (B.w0 == 0 || B.w1 == 0 || B.w2 == 0) return DMS_OK;
     const int64_t owned = B.w0 * B.w1 * B.w2;
-    if (mark) {
-        const int64_t words = (owned + 31) / 32;
-        hipLaunchKernelGGL(k_mark_zero, dim3((unsigned)((words + kThreads - 1) / kThreads)), dim3(kThreads), 0, s,
-                           mark, words);
-    }
     constexpr int kGX = kTileX[0], kGY = kTileVerts / kGX;
     const int64_t bxc = (B.w0 + kGX - 1) / kGX, byc = (B.w1 + kGY - 1) / kGY;
     const int64_t blocks = bxc * byc * B.w2;
     if (blocks > 2147483647LL) return DMS_E_SIZE;
-    const Handoff H = handoff_begin(ws, owned, s);
-    hipLaunchKernelGGL((k_gradient<Keys, kGX, kGY>), dim3((unsigned)blocks), dim3(kThreads), 0, s, field, B, bxc,
-                       (uint4 *)rec, defect8_table(), H, flags, mark);
+    const bool whole = blocks <= kWholeTiles;
+    const Handoff H = handoff_carve(whole ? nullptr : ws, owned);
+    gradient_begin(mark, owned, H, s);
+    if (!whole)
+        hipLaunchKernelGGL((k_gradient<Keys, kGX, kGY>), dim3((unsigned)blocks), dim3(kThreads), 0, s, field, B, bxc,
+                           (uint4 *)rec, defect8_table(), H, flags, mark);
     hipLaunchKernelGGL((k_gradient_dense<Keys, kGX, kGY>), dim3(dense_blocks(blocks)), dim3(kThreads), 0, s, field,
-                       B, bxc, (uint32_t)blocks, (uint4 *)rec, H, mark);
+                       B, bxc, (uint32_t)blocks, whole, (uint4 *)rec, H, whole ? flags : nullptr, mark);
     queue_finish(H, rec, mark, s);
     return launch_status();
 }
@@ -1336,19 +1350,17 @@ int launch_gradient_batch(int variant, const int32_t *order, const BatchField *f
     (void)nfields;
     if (total_tiles == 0) return DMS_OK;
     if (total_tiles > 2147483647LL) return DMS_E_SIZE;
-    if (mark) {
-        const int64_t words = (total_verts + 31) / 32;
-        hipLaunchKernelGGL(k_mark_zero, dim3((unsigned)((words + kThreads - 1) / kThreads)), dim3(kThreads), 0, s,
-                           mark, words);
-    }
     const uint4 *d8 = defect8_table();
-    const Handoff H = handoff_begin(ws, total_verts, s);
+    const bool whole = total_tiles <= kWholeTiles;
+    const Handoff H = handoff_carve(whole ? nullptr : ws, total_verts);
+    gradient_begin(mark, total_verts, H, s);
     const BatchTiles L{fields, tile_start, tile_field};
 #define DMS_LAUNCH(GXV)                                                                                             \
-    hipLaunchKernelGGL((k_gradient_batch<GXV, kTileVerts / GXV>), dim3((unsigned)total_tiles), dim3(kThreads), 0, s, \
-                       order, L, (uint4 *)rec, d8, H, mark);                                                         \
+    if (!whole)                                                                                                      \
+        hipLaunchKernelGGL((k_gradient_batch<GXV, kTileVerts / GXV>), dim3((unsigned)total_tiles), dim3(kThreads),   \
+                           0, s, order, L, (uint4 *)rec, d8, H, mark);                                               \
     hipLaunchKernelGGL((k_gradient_dense_batch<GXV, kTileVerts / GXV>), dim3(dense_blocks(total_tiles)),             \
-                       dim3(kThreads), 0, s, order, L, (uint32_t)total_tiles, (uint4 *)rec, H, mark)
+                       dim3(kThreads), 0, s, order, L, (uint32_t)total_tiles, whole, (uint4 *)rec, H, mark)
     switch (variant) {
     case 0: DMS_LAUNCH(64); break;
     case 1: DMS_LAUNCH(32); break;

@@ -12,13 +12,16 @@ pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 
-# tiles hold 64 x 16 x 1 vertices and 256 general ones make a tile dense
+# tiles hold 64 x 16 x 1 vertices, 256 general ones make a tile dense, and a
+# launch of at most 256 tiles leaves everything to the dense kernel
 SHAPES = [
     (1, 1, 5000),   # one vertex a tile: the queue fills, then the list
     (3, 2, 900),    # six vertices a tile: the queue fills, the list does not
-    (16, 16, 96),   # 256 vertices a tile, just below and at the threshold
+    (16, 16, 300),  # 256 vertices a tile, just below and at the threshold
     (64, 16, 5),    # a few full tiles, dealt in quarters
-    (67, 18, 31),   # ragged tiles beside full ones
+    (64, 16, 256),  # the most tiles that the dense kernel takes alone
+    (64, 16, 257),  # one more
+    (67, 18, 80),   # ragged tiles beside full ones, a list dealt in quarters
     (64, 16, 450),  # more full tiles than a quarter of the dense grid
 ]
 

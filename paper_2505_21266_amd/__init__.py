@@ -127,9 +127,14 @@ def init(device=None):
     _ready.add(idx)
 
 
+_Int64x3, _Int64x4 = ctypes.c_int64 * 3, ctypes.c_int64 * 4
+
+
 def _arr3(v):
-    a = np.ascontiguousarray(np.asarray(v, dtype=np.int64).reshape(3))
-    return a, a.ctypes.data_as(ctypes.c_void_p)
+    """Three host int64 as a ctypes array (twice: to keep, and to pass as the pointer)."""
+    x, y, z = v
+    a = _Int64x3(int(x), int(y), int(z))
+    return a, a
 
 
 def _ptr(t):
@@ -195,9 +200,30 @@ def new_flags(device):
     return torch.zeros(1, dtype=torch.int32, device=device)
 
 
+def _fetch(*tensors):
+    """Host copies (flat numpy arrays) of GPU tensors of one device: the copies
+    are enqueued into one pinned buffer and waited for once."""
+    import torch
+    at, nbytes = [], 0
+    for t in tensors:
+        at.append(nbytes)
+        nbytes += (t.numel() * t.element_size() + 15) // 16 * 16
+    host = torch.empty(max(nbytes, 16), dtype=torch.uint8, pin_memory=True)
+    out = []
+    for t, a in zip(tensors, at):
+        h = host[a:a + t.numel() * t.element_size()].view(t.dtype)
+        h.copy_(t.reshape(-1), non_blocking=True)
+        out.append(h.numpy())
+    torch.cuda.current_stream(tensors[0].device).synchronize()
+    return out
+
+
 def check_flags(flags, allow=0):
     """Synchronises and raises if a device flag beyond `allow` is set."""
-    f = int(flags.item())
+    return _raise_flags(int(flags.item()), allow)
+
+
+def _raise_flags(f, allow=0):
     if f & ~allow & FLAG_NAN:
         raise ValueError("NaN in the input field")
     if f & ~allow & FLAG_CAPACITY:
@@ -359,8 +385,23 @@ def critical_simplices(rec, dims, lo=None, hi=None, cap=None, flags=None, counts
     wrote with rec (only flagged records are read), or None.  Returns
     (lists, counts tensor).
     """
-    import torch
     _require_gpu(rec, "rec")
+    own_flags, sized = flags is None, cap is not None
+    if not sized:
+        cap, counts, _ = _count_cells(rec, dims, lo, hi, mask, counts)
+        if not own_flags:
+            flags.zero_()
+    lists, counts, flags = _list_cells(rec, dims, lo, hi, cap, mask, counts, flags)
+    # lists sized by a counting call cannot overflow, and nothing else is flagged
+    if own_flags and sized:
+        check_flags(flags)
+    return lists, counts
+
+
+def _list_cells(rec, dims, lo, hi, cap, mask, counts=None, flags=None):
+    """The extraction into new lists of the given capacities; returns (lists,
+    counts, flags)."""
+    import torch
     dev = rec.device
     lo, hi = _box(dims, lo, hi)
     d, dp = _arr3(dims)
@@ -368,30 +409,27 @@ def critical_simplices(rec, dims, lo=None, hi=None, cap=None, flags=None, counts
     h, hp = _arr3(hi)
     L = lib()
     mp = _mask_ptr(mask, max(0, hi[0] - lo[0]) * max(0, hi[1] - lo[1]) * max(0, hi[2] - lo[2]))
-    nbytes = L.dms_critical_workspace_size(dp, lp, hp)
-    ws = _ws_crit.get(nbytes, dev)
+    ws = _ws_crit.get(L.dms_critical_workspace_size(dp, lp, hp), dev)
     if counts is None:
         counts = torch.zeros(4, dtype=torch.int64, device=dev)
-    own_flags = flags is None
-    if own_flags:
+    if flags is None:
         flags = new_flags(dev)
-    st = _stream(rec)
-    if cap is None:
-        zc = np.zeros(4, np.int64)
-        _check(L.dms_critical_simplices(_ptr(rec), mp, dp, lp, hp, None, None, None, None,
-                                        zc.ctypes.data_as(ctypes.c_void_p), _ptr(counts), _ptr(ws),
-                                        ws.numel(), _ptr(flags), st), "dms_critical_simplices")
-        cap = counts.cpu().numpy().copy()
-        flags.zero_()
-    capa = np.ascontiguousarray(np.asarray(cap, dtype=np.int64).reshape(4))
-    lists = [torch.empty(int(max(c, 0)), dtype=torch.int64, device=dev) for c in capa]
+    capa = _Int64x4(*(int(c) for c in np.asarray(cap).reshape(4)))
+    lists = [torch.empty(max(c, 0), dtype=torch.int64, device=dev) for c in capa]
     _check(L.dms_critical_simplices(_ptr(rec), mp, dp, lp, hp, _ptr(lists[0]), _ptr(lists[1]),
-                                    _ptr(lists[2]), _ptr(lists[3]),
-                                    capa.ctypes.data_as(ctypes.c_void_p), _ptr(counts), _ptr(ws),
-                                    ws.numel(), _ptr(flags), st), "dms_critical_simplices")
-    if own_flags:
-        check_flags(flags)
-    return lists, counts
+                                    _ptr(lists[2]), _ptr(lists[3]), capa, _ptr(counts), _ptr(ws),
+                                    ws.numel(), _ptr(flags), _stream(rec)), "dms_critical_simplices")
+    return lists, counts, flags
+
+
+def _count_cells(rec, dims, lo, hi, mask, counts=None, flags=None):
+    """Counts the critical cells (a call whose lists have no room) and waits:
+    (host counts, counts tensor, the host value of flags, 0 without)."""
+    _, counts, _ = _list_cells(rec, dims, lo, hi, (0, 0, 0, 0), mask, counts)
+    if flags is None:
+        return _fetch(counts)[0], counts, 0
+    cap, f = _fetch(counts, flags)
+    return cap, counts, int(f[0])
 
 
 def critical_simplices_noalloc(rec, dims, cap, lo=None, hi=None, lists=None, counts=None, flags=None,
@@ -410,7 +448,7 @@ def critical_simplices_noalloc(rec, dims, cap, lo=None, hi=None, lists=None, cou
     d, dp = _arr3(dims)
     l, lp = _arr3(lo)
     h, hp = _arr3(hi)
-    capa = np.ascontiguousarray(np.asarray(cap, dtype=np.int64).reshape(4))
+    capa = _Int64x4(*(int(c) for c in np.asarray(cap).reshape(4)))
     if lists is None:
         lists = [torch.empty(int(max(c, 0)), dtype=torch.int64, device=dev) for c in capa]
     if counts is None:
@@ -420,7 +458,7 @@ def critical_simplices_noalloc(rec, dims, cap, lo=None, hi=None, lists=None, cou
     mp = _mask_ptr(mask, max(0, hi[0] - lo[0]) * max(0, hi[1] - lo[1]) * max(0, hi[2] - lo[2]))
     _check(lib().dms_critical_simplices_noalloc(_ptr(rec), mp, dp, lp, hp, _ptr(lists[0]), _ptr(lists[1]),
                                                 _ptr(lists[2]), _ptr(lists[3]),
-                                                capa.ctypes.data_as(ctypes.c_void_p), _ptr(counts),
+                                                capa, _ptr(counts),
                                                 _ptr(flags), _stream(rec)),
            "dms_critical_simplices_noalloc")
     return lists, counts
@@ -544,27 +582,23 @@ def d0_pairs(rec, order_t, dims, crit0, crit1):
     tri_min0 = torch.empty(max(n1, 1), dtype=torch.int32, device=dev)
     tri_min1 = torch.empty(max(n1, 1), dtype=torch.int32, device=dev)
     min_order = torch.empty(max(n0, 1), dtype=torch.int32, device=dev)
-    ntri = torch.zeros(1, dtype=torch.int64, device=dev)
-    flags = new_flags(dev)
+    meta = torch.zeros(2, dtype=torch.int64, device=dev)  # the triplets' number, the flags
+    ntri, flags = meta[:1], meta.view(torch.int32)[2:3]
     ws = torch.empty(max(int(L.dms_d0_workspace_size(dp, n1)), 256), dtype=torch.uint8, device=dev)
     _check(L.dms_d0_triplets(_ptr(rec), _ptr(order_t), dp, _ptr(crit0), n0, _ptr(crit1), n1,
                              _ptr(tri_edge), _ptr(tri_min0), _ptr(tri_min1), _ptr(min_order),
                              _ptr(ntri), _ptr(ws), ws.numel(), _ptr(flags), _stream(rec)),
            "dms_d0_triplets")
-    check_flags(flags)
-    k = int(ntri.item())
-    te = np.ascontiguousarray(tri_edge[:k].cpu().numpy())
-    t0 = np.ascontiguousarray(tri_min0[:k].cpu().numpy())
-    t1 = np.ascontiguousarray(tri_min1[:k].cpu().numpy())
-    mo = np.ascontiguousarray(min_order[:n0].cpu().numpy())
-    c0 = crit0.cpu().numpy()
-    cap = max(k, 1)
-    pe = np.zeros(cap, np.int64)
-    pm = np.zeros(cap, np.int32)
+    k, f = (int(x) for x in _fetch(meta)[0])
+    _raise_flags(f & 0xffffffff)
+    te, t0, t1, mo, c0 = _fetch(tri_edge[:k], tri_min0[:k], tri_min1[:k], min_order[:n0], crit0)
+    cap = max(min(k, n0), 1)  # every pair ends one of the minima
+    pe = np.empty(cap, np.int64)
+    pm = np.empty(cap, np.int32)
     npairs = np.zeros(1, np.int64)
-    _check(L.dms_d0_pairs_sorted_host(te.ctypes.data_as(P), t0.ctypes.data_as(P), t1.ctypes.data_as(P),
-                                      k, mo.ctypes.data_as(P), n0, pe.ctypes.data_as(P),
-                                      pm.ctypes.data_as(P), cap, npairs.ctypes.data_as(P)),
+    _check(L.dms_d0_pairs_sorted_host(te.ctypes.data, t0.ctypes.data, t1.ctypes.data,
+                                      k, mo.ctypes.data, n0, pe.ctypes.data,
+                                      pm.ctypes.data, cap, npairs.ctypes.data),
            "dms_d0_pairs_sorted_host")
     m = int(npairs[0])
     return pe[:m], (c0[pm[:m]] >> 8).astype(np.int64)
@@ -587,27 +621,23 @@ def d2_pairs(rec, order_t, dims, crit2, crit3):
     tri_max0 = torch.empty(max(n2, 1), dtype=torch.int32, device=dev)
     tri_max1 = torch.empty(max(n2, 1), dtype=torch.int32, device=dev)
     max_rank = torch.empty(max(n3, 1), dtype=torch.int32, device=dev)
-    ntri = torch.zeros(1, dtype=torch.int64, device=dev)
-    flags = new_flags(dev)
+    meta = torch.zeros(2, dtype=torch.int64, device=dev)  # the triplets' number, the flags
+    ntri, flags = meta[:1], meta.view(torch.int32)[2:3]
     ws = torch.empty(max(int(L.dms_d2_workspace_size(n2, n3)), 256), dtype=torch.uint8, device=dev)
     _check(L.dms_d2_triplets(_ptr(rec), _ptr(order_t), dp, _ptr(crit2), n2, _ptr(crit3), n3,
                              _ptr(tri_code), _ptr(tri_max0), _ptr(tri_max1), _ptr(max_rank),
                              _ptr(ntri), _ptr(ws), ws.numel(), _ptr(flags), _stream(rec)),
            "dms_d2_triplets")
-    check_flags(flags)
-    k = int(ntri.item())
-    tc = np.ascontiguousarray(tri_code[:k].cpu().numpy())
-    t0 = np.ascontiguousarray(tri_max0[:k].cpu().numpy())
-    t1 = np.ascontiguousarray(tri_max1[:k].cpu().numpy())
-    mr = np.ascontiguousarray(max_rank[:n3].cpu().numpy())
-    c3 = crit3.cpu().numpy()
-    cap = max(k, 1)
-    pt = np.zeros(cap, np.int64)
-    pm = np.zeros(cap, np.int32)
+    k, f = (int(x) for x in _fetch(meta)[0])
+    _raise_flags(f & 0xffffffff)
+    tc, t0, t1, mr, c3 = _fetch(tri_code[:k], tri_max0[:k], tri_max1[:k], max_rank[:n3], crit3)
+    cap = max(min(k, n3), 1)  # every pair ends one of the maxima (the outside node never ends)
+    pt = np.empty(cap, np.int64)
+    pm = np.empty(cap, np.int32)
     npairs = np.zeros(1, np.int64)
-    _check(L.dms_d2_pairs_sorted_host(tc.ctypes.data_as(P), t0.ctypes.data_as(P), t1.ctypes.data_as(P),
-                                      k, mr.ctypes.data_as(P), n3, pt.ctypes.data_as(P),
-                                      pm.ctypes.data_as(P), cap, npairs.ctypes.data_as(P)),
+    _check(L.dms_d2_pairs_sorted_host(tc.ctypes.data, t0.ctypes.data, t1.ctypes.data,
+                                      k, mr.ctypes.data, n3, pt.ctypes.data,
+                                      pm.ctypes.data, cap, npairs.ctypes.data),
            "dms_d2_pairs_sorted_host")
     m = int(npairs[0])
     return pt[:m], c3[pm[:m]].astype(np.int64)
@@ -617,13 +647,21 @@ def gradient_pipeline(values, lo=None, hi=None, cap=None):
     """order -> discrete gradient -> critical simplices for one field (the
     gradient marks the records holding critical cells; the extraction reads
     only those)."""
-    o = order(values)
+    flags = new_flags(values.device)
+    o = order(values, flags=flags, check=False)
     dims = dims_of(values)
     blo, bhi = _box(dims, lo, hi)
     mask = critical_mask(max(0, bhi[0] - blo[0]) * max(0, bhi[1] - blo[1]) * max(0, bhi[2] - blo[2]),
                          values.device)
     rec = discrete_gradient(o, lo, hi, mask=mask)
-    lists, counts = critical_simplices(rec, dims, lo, hi, cap=cap, mask=mask)
+    if cap is not None:
+        lists, counts, flags = _list_cells(rec, dims, lo, hi, cap, mask, flags=flags)
+        check_flags(flags)
+        return o, rec, lists, counts
+    # one wait, for the counts that size the lists; a NaN is found there too
+    cap, counts, f = _count_cells(rec, dims, lo, hi, mask, flags=flags)
+    _raise_flags(f)
+    lists, counts, _ = _list_cells(rec, dims, lo, hi, cap, mask, counts)
     return o, rec, lists, counts
 
 

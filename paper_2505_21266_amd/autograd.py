@@ -18,8 +18,7 @@ def _torch():
 
 def _make():
     torch = _torch()
-    from . import (critical_simplices, d0_pairs, d2_pairs, dims_of, discrete_gradient, gradient_backward,
-                   order, simplex_values)
+    from . import d0_pairs, d2_pairs, dims_of, gradient_backward, gradient_pipeline, simplex_values
 
     def _backward(ctx, g_births, g_deaths):
         birth_code, death_code = ctx.saved_tensors
@@ -46,9 +45,7 @@ def _make():
         def forward(ctx, field):
             dims = dims_of(field)
             with torch.no_grad():
-                o = order(field)
-                rec = discrete_gradient(o)
-                lists, counts = critical_simplices(rec, dims)
+                o, rec, lists, _ = gradient_pipeline(field)
                 pe, pm = d0_pairs(rec, o, dims, lists[0], lists[1])
             dev = field.device
             death_code = torch.from_numpy(pe).to(dev)
@@ -68,9 +65,7 @@ def _make():
         def forward(ctx, field):
             dims = dims_of(field)
             with torch.no_grad():
-                o = order(field)
-                rec = discrete_gradient(o)
-                lists, counts = critical_simplices(rec, dims)
+                o, rec, lists, _ = gradient_pipeline(field)
                 pt, pq = d2_pairs(rec, o, dims, lists[2], lists[3])
             dev = field.device
             birth_code = torch.from_numpy(pt).to(dev)

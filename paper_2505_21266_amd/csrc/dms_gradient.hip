@@ -187,14 +187,88 @@ struct F64Keys {
     __device__ static C cmp(H h, int slot) { return h == kAbsentH ? c_highest<C>() : ((C)h << 4) | (C)slot; }
 };
 
+// Comparisons that are only counted or collected into a mask: the compare's
+// lane mask goes to a scalar pair and from there into the carry of an addition,
+// one vector instruction each (the compiler selects 0 or 1 by the mask, then
+// ORs or adds, and fills the two wait states between a compare and the read of
+// its mask with nops).  Three scalar pairs in turn put two other instructions
+// between each compare and its use.  T: the comparison's type.
+#define DMS_CMP(T, s, a, b) "v_cmp_lt_" T "_e64 %[s" #s "], %[" #a "], %[" #b "]\n\t"
+#define DMS_BIT(l, s) "v_addc_co_u32_e64 %[" #l "], vcc, %[" #l "], %[" #l "], %[s" #s "]\n\t"  // l = 2 l + mask
+#define DMS_INC(l, s) "v_addc_co_u32_e64 %[" #l "], vcc, 0, %[" #l "], %[s" #s "]\n\t"      // l = l + mask
+#define DMS_SET(l, s) "v_cndmask_b32_e64 %[" #l "], 0, 1, %[s" #s "]\n\t"                   // l = mask
+
+#define DMS_LOWER_MASK(T)                                                                                          \
+    DMS_CMP(T, 0, o13, x) DMS_CMP(T, 1, o12, x) DMS_CMP(T, 2, o11, x) DMS_SET(l, 0)                                 \
+    DMS_CMP(T, 0, o10, x) DMS_BIT(l, 1) DMS_CMP(T, 1, o9, x) DMS_BIT(l, 2)                                         \
+    DMS_CMP(T, 2, o8, x) DMS_BIT(l, 0) DMS_CMP(T, 0, o7, x) DMS_BIT(l, 1)                                          \
+    DMS_CMP(T, 1, o6, x) DMS_BIT(l, 2) DMS_CMP(T, 2, o5, x) DMS_BIT(l, 0)                                          \
+    DMS_CMP(T, 0, o4, x) DMS_BIT(l, 1) DMS_CMP(T, 1, o3, x) DMS_BIT(l, 2)                                          \
+    DMS_CMP(T, 2, o2, x) DMS_BIT(l, 0) DMS_CMP(T, 0, o1, x) DMS_BIT(l, 1)                                          \
+    DMS_CMP(T, 1, o0, x) DMS_BIT(l, 2) "s_nop 0\n\t" DMS_BIT(l, 0) "s_nop 0\n\t" DMS_BIT(l, 1)
+
 // Lower-neighbour mask of x: bit e set if neighbour e precedes x.
 template <typename C>
 __device__ __forceinline__ uint32_t lower_mask(const C *o, C ox)
 {
     uint32_t low = 0;
+    if constexpr (sizeof(C) > 8) {
 #pragma unroll
-    for (int e = 0; e < 14; ++e) low |= (o[e] < ox ? 1u : 0u) << e;
+        for (int e = 0; e < 14; ++e) low |= (o[e] < ox ? 1u : 0u) << e;
+    } else {
+        uint64_t s0, s1, s2;
+#define DMS_OPERANDS                                                                                                \
+    : [l] "=&v"(low), [s0] "=&s"(s0), [s1] "=&s"(s1), [s2] "=&s"(s2)                                                \
+    : [x] "v"(ox), [o0] "v"(o[0]), [o1] "v"(o[1]), [o2] "v"(o[2]), [o3] "v"(o[3]), [o4] "v"(o[4]), [o5] "v"(o[5]),     \
+      [o6] "v"(o[6]), [o7] "v"(o[7]), [o8] "v"(o[8]), [o9] "v"(o[9]), [o10] "v"(o[10]), [o11] "v"(o[11]),             \
+      [o12] "v"(o[12]), [o13] "v"(o[13])                                                                            \
+    : "vcc"
+        if constexpr (sizeof(C) == 4) asm(DMS_LOWER_MASK("i32") DMS_OPERANDS);
+        else asm(DMS_LOWER_MASK("f64") DMS_OPERANDS);
+#undef DMS_OPERANDS
+    }
     return low;
+}
+
+// Lehmer digits of eight values: l[i] = how many of the later ones are smaller.
+#define DMS_DIGITS(T)                                                                                              \
+    DMS_CMP(T, 0, v7, v6) DMS_CMP(T, 1, v7, v5) DMS_CMP(T, 2, v7, v4) DMS_SET(l6, 0)                                \
+    DMS_CMP(T, 0, v7, v3) DMS_SET(l5, 1) DMS_CMP(T, 1, v7, v2) DMS_SET(l4, 2)                                      \
+    DMS_CMP(T, 2, v7, v1) DMS_SET(l3, 0) DMS_CMP(T, 0, v7, v0) DMS_SET(l2, 1)                                      \
+    DMS_CMP(T, 1, v6, v5) DMS_SET(l1, 2) DMS_CMP(T, 2, v6, v4) DMS_SET(l0, 0)                                      \
+    DMS_CMP(T, 0, v6, v3) DMS_INC(l5, 1) DMS_CMP(T, 1, v6, v2) DMS_INC(l4, 2)                                      \
+    DMS_CMP(T, 2, v6, v1) DMS_INC(l3, 0) DMS_CMP(T, 0, v6, v0) DMS_INC(l2, 1)                                      \
+    DMS_CMP(T, 1, v5, v4) DMS_INC(l1, 2) DMS_CMP(T, 2, v5, v3) DMS_INC(l0, 0)                                      \
+    DMS_CMP(T, 0, v5, v2) DMS_INC(l4, 1) DMS_CMP(T, 1, v5, v1) DMS_INC(l3, 2)                                      \
+    DMS_CMP(T, 2, v5, v0) DMS_INC(l2, 0) DMS_CMP(T, 0, v4, v3) DMS_INC(l1, 1)                                      \
+    DMS_CMP(T, 1, v4, v2) DMS_INC(l0, 2) DMS_CMP(T, 2, v4, v1) DMS_INC(l3, 0)                                      \
+    DMS_CMP(T, 0, v4, v0) DMS_INC(l2, 1) DMS_CMP(T, 1, v3, v2) DMS_INC(l1, 2)                                      \
+    DMS_CMP(T, 2, v3, v1) DMS_INC(l0, 0) DMS_CMP(T, 0, v3, v0) DMS_INC(l2, 1)                                      \
+    DMS_CMP(T, 1, v2, v1) DMS_INC(l1, 2) DMS_CMP(T, 2, v2, v0) DMS_INC(l0, 0)                                      \
+    DMS_CMP(T, 0, v1, v0) DMS_INC(l1, 1) "s_nop 0\n\t" DMS_INC(l0, 2) "s_nop 0\n\t" DMS_INC(l0, 0)
+
+template <typename C>
+__device__ __forceinline__ void lehmer_digits(const C *v, uint32_t *l)
+{
+    if constexpr (sizeof(C) > 8) {
+#pragma unroll
+        for (int i = 0; i < 7; ++i) {
+            l[i] = 0;
+#pragma unroll
+            for (int k = i + 1; k < 8; ++k) l[i] += v[k] < v[i] ? 1u : 0u;
+        }
+    } else {
+        uint64_t s0, s1, s2;
+#define DMS_OPERANDS                                                                                                \
+    : [l0] "=&v"(l[0]), [l1] "=&v"(l[1]), [l2] "=&v"(l[2]), [l3] "=&v"(l[3]), [l4] "=&v"(l[4]), [l5] "=&v"(l[5]),     \
+      [l6] "=&v"(l[6]), [s0] "=&s"(s0), [s1] "=&s"(s1), [s2] "=&s"(s2)                                              \
+    : [v0] "v"(v[0]), [v1] "v"(v[1]), [v2] "v"(v[2]), [v3] "v"(v[3]), [v4] "v"(v[4]), [v5] "v"(v[5]), [v6] "v"(v[6]), \
+      [v7] "v"(v[7])                                                                                                \
+    : "vcc"
+        if constexpr (sizeof(C) == 4) asm(DMS_DIGITS("i32") DMS_OPERANDS);
+        else asm(DMS_DIGITS("f64") DMS_OPERANDS);
+#undef DMS_OPERANDS
+    }
 }
 
 // Batcher's odd-even merge sort of 16 inputs, without the comparators that
@@ -450,7 +524,6 @@ __device__ __forceinline__ bool process_vertex(const typename Keys::C *o, typena
 // and kept in a device table; such vertices then cost a table lookup.
 constexpr int kPerm7 = 5040;
 constexpr int kRegular = 128 * kPerm7;
-__device__ uint4 g_regular[kRegular];
 
 // One-defect vertices: six pairs have one lower member and the seventh has
 // both (8 lower neighbours) or neither (6).  All three families are looked
@@ -468,27 +541,23 @@ __device__ uint4 g_regular[kRegular];
 // j beyond the table offset.
 //   regular: index side * 7! + code7                       (10 MB)
 //   |L| = 6: index (j * 64 + side6) * 7! + code7            (36 MB, sparse)
-//   |L| = 8: index (j * 64 + side6) * 8! + code8            (289 MB, allocated
-//            once per device)
-// side6 is the 7-bit side pattern with bit j removed.
+//   |L| = 8: index (j * 64 + side6) * 8! + code8            (289 MB)
+// side6 is the 7-bit side pattern with bit j removed.  The three follow each
+// other in one allocation per device, so that a lookup is one 32-bit entry
+// number from one base; after the entries come the flags, one bit per entry:
+// whether its lower star holds a critical cell.
 constexpr int kPerm8 = 40320;
 constexpr int kDefect6 = 7 * 64 * kPerm7;
-constexpr int64_t kDefect8 = 7ll * 64 * kPerm8;
-__device__ uint4 g_defect6[kDefect6];
-// One bit per table entry: whether the entry's lower star holds a critical
-// cell (set by the table fillers, read to mark records for the extraction).
-static_assert(kRegular % 64 == 0 && kDefect6 % 64 == 0 && kDefect8 % 64 == 0, "flag words per wave");
-__device__ uint32_t g_regular_flags[kRegular / 32];
-__device__ uint32_t g_defect6_flags[kDefect6 / 32];
-__device__ uint32_t g_defect8_flags[kDefect8 / 32];
+constexpr int kDefect8 = 7 * 64 * kPerm8;
+constexpr uint32_t kFirst6 = kRegular, kFirst8 = kFirst6 + kDefect6, kEntries = kFirst8 + kDefect8;
+static_assert(kFirst6 % 64 == 0 && kFirst8 % 64 == 0 && kEntries % 64 == 0, "flag words per wave");
+static_assert((uint64_t)kEntries * sizeof(uint4) < (1ull << 32), "32-bit byte offsets");
+constexpr size_t kTableBytes = (size_t)kEntries * sizeof(uint4) + kEntries / 8;
 
-// A table lookup: the entry's record (null when x is in no tabulated
-// family), the family's flag bits and the entry index.
-struct TabHit {
-    const uint4 *rec;
-    const uint32_t *flags;
-    uint32_t idx;
-};
+__device__ __forceinline__ const uint32_t *table_flags(const uint4 *table)
+{
+    return (const uint32_t *)(table + kEntries);
+}
 
 // Whether x, with lower neighbours low, is in none of the tabulated families
 // (at least two of the opposite pairs wholly lower or wholly upper).
@@ -497,15 +566,24 @@ __device__ __forceinline__ bool general_vertex(uint32_t low)
     return __popc((low ^ (__brev(low) >> 18)) & 0x7fu) < 6;
 }
 
-// Table entry of x, or a null record when x is in none of the families.
+// m ? a : b for a mask m of all ones or all zeros.
+__device__ __forceinline__ int32_t pick(uint32_t m, int32_t a, int32_t b)
+{
+    return (int32_t)(((uint32_t)a & m) | ((uint32_t)b & ~m));
+}
+__device__ __forceinline__ double pick(uint32_t m, double a, double b) { return m ? a : b; }
+__device__ __forceinline__ unsigned __int128 pick(uint32_t m, unsigned __int128 a, unsigned __int128 b)
+{
+    return m ? a : b;
+}
+
+// Table entry of x (not a general vertex).
 template <typename C>
-__device__ __forceinline__ TabHit table_entry(uint32_t low, const C *o, const uint4 *__restrict__ defect8)
+__device__ __forceinline__ uint32_t table_entry(uint32_t low, const C *o)
 {
     const C kHigh = c_highest<C>();
     const uint32_t rev = __brev(low) >> 18;  // bit e -> bit 13 - e
     const uint32_t one = (low ^ rev) & 0x7fu;
-    const int npair = __popc(one);
-    if (npair < 6) return TabHit{nullptr, nullptr, 0};
     const uint32_t side = __brev((low >> 7) & 0x7fu) >> 25;  // bit i: the lower member is 13 - i
     const uint32_t both = low & rev & 0x7fu;                   // pairs wholly lower
     // slot values without selecting between array elements by a per-lane
@@ -514,43 +592,29 @@ __device__ __forceinline__ TabHit table_entry(uint32_t low, const C *o, const ui
     // pair (side bit set) takes neighbour 13 - i, and neighbour i goes to
     // slot 7
     C v[8];
-    C v7 = kHigh;
+    v[7] = kHigh;
 #pragma unroll
     for (int i = 0; i < 7; ++i) {
         const C a = o[i], b = o[13 - i];
-        const bool w = (both >> i) & 1u;
-        v[i] = w ? b : cmin(a, b);
-        v7 = cmin(v7, w ? a : kHigh);
+        const uint32_t w = (uint32_t)((int32_t)(both << (31 - i)) >> 31);
+        v[i] = pick(w, b, cmin(a, b));
+        v[7] = cmin(v[7], pick(w, a, kHigh));
     }
-    const bool eight = both != 0;
-    v[7] = v7;
-    uint32_t l[8];
+    uint32_t l[7];
+    lehmer_digits(v, l);
+    // factorial sums of the digits, by Horner's rule
+    uint32_t code7 = l[0], code8 = l[0];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        l[i] = 0;
-#pragma unroll
-        for (int k = i + 1; k < 8; ++k) l[i] += v[k] < v[i] ? 1u : 0u;
+    for (int i = 1; i < 7; ++i) {
+        code7 = code7 * (uint32_t)(7 - i) + l[i];
+        code8 = code8 * (uint32_t)(8 - i) + l[i];
     }
-    constexpr uint32_t f7[7] = {720, 120, 24, 6, 2, 1, 1};
-    constexpr uint32_t f8[8] = {5040, 720, 120, 24, 6, 2, 1, 1};
-    uint32_t code7 = 0, code8 = 0;
-#pragma unroll
-    for (int i = 0; i < 7; ++i) code7 += l[i] * f7[i];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) code8 += l[i] * f8[i];
-    if (npair == 7) {
-        const uint32_t i = side * kPerm7 + code7;
-        return TabHit{&g_regular[i], g_regular_flags, i};
-    }
-    const uint32_t j = (uint32_t)__ffs(~one & 0x7fu) - 1u;
+    const bool eight = both != 0, regular = one == 0x7fu;
+    const uint32_t j = (uint32_t)__builtin_ctz(~one | 0x80u);  // (7 for a regular vertex)
     const uint32_t side6 = (side & ((1u << j) - 1u)) | ((side >> (j + 1u)) << j);
-    static_assert(kDefect8 < (1ll << 32), "32-bit index into the wholly-lower table");
-    if (eight) {
-        const uint32_t i = (j * 64u + side6) * (uint32_t)kPerm8 + code8;
-        return TabHit{defect8 + i, g_defect8_flags, i};
-    }
-    const uint32_t i = (j * 64u + side6) * kPerm7 + code7;
-    return TabHit{&g_defect6[i], g_defect6_flags, i};
+    const uint32_t group = regular ? side : j * 64u + side6;
+    const uint32_t first = eight ? kFirst8 : regular ? 0u : kFirst6;
+    return __umul24(group, eight ? (uint32_t)kPerm8 : (uint32_t)kPerm7) + (eight ? code8 : code7) + first;
 }
 
 template <int GX, int GY>
@@ -749,9 +813,9 @@ __device__ __forceinline__ void stage_halo(const void *__restrict__ field, const
 }
 
 // A wave whose first row of the tile is mostly general vertices (a noisy
-// field) leaves the table vertices of its other rows to the general path too:
-// the table index costs every lane of a row that has one.  in, gen: whether
-// this lane's vertex of the first row lies in the box, and is general.
+// field) leaves all its vertices to the general path: the table index costs
+// every lane of a row that has one.  in, gen: whether this lane's vertex of
+// the first row lies in the box, and is general.
 __device__ __forceinline__ bool skip_tables(bool in, bool gen)
 {
     const int n = __popcll(__ballot(in)), g = __popcll(__ballot(in && gen));
@@ -770,7 +834,7 @@ struct TileShared {
 template <typename Keys, int GX, int GY>
 __device__ __forceinline__ void gradient_tile(const void *__restrict__ field, const Box &B, int64_t bx, int64_t by,
                                               int64_t bz, uint32_t tile_no, uint4 *__restrict__ rec,
-                                              const uint4 *__restrict__ defect8, const Handoff &H, uint32_t *flags,
+                                              const uint4 *__restrict__ table, const Handoff &H, uint32_t *flags,
                                               uint32_t *__restrict__ mark, TileShared &sh,
                                               typename Keys::H *tile)
 {
@@ -801,25 +865,27 @@ __device__ __forceinline__ void gradient_tile(const void *__restrict__ field, co
         const int v = tid + k * kThreads;
         const int tx = GX == kWave ? tid % kWave : v % GX;
         const int ty = GX == kWave ? wave_u + (kThreads / kWave) * k : v / GX;
-        TabHit hit{nullptr, g_regular_flags, 0};
-        if (bx * GX + tx < w0 && by * GY + ty < w1 && bz < w2) {
-            if (!skip) {
-                const int c = (tx + 1) + S::HX * ((ty + 1) + S::HY);
-                C o[14], ox;
-                gather_orders<Keys, GX, GY>(tile, c, o, ox);
-                hit = table_entry(lower_mask(o, ox), o, defect8);
+        const bool in = bx * GX + tx < w0 && by * GY + ty < w1;
+        uint32_t idx = 0;
+        if (in) state |= 1u << k;
+        if (!skip) {
+            C o[14], ox;
+            gather_orders<Keys, GX, GY>(tile, (tx + 1) + S::HX * ((ty + 1) + S::HY), o, ox);
+            const uint32_t low = lower_mask(o, ox);
+            const bool gen = general_vertex(low);
+            if (k == 0) skip = skip_tables(in, gen);
+            if (in && !gen && !skip) {
+                idx = table_entry(low, o);
+                state |= 1u << (kPer + k);
             }
-            state |= 1u << k;
         }
-        if (k == 0) skip = skip_tables(state & 1u, !hit.rec);
-        if (hit.rec) state |= 1u << (kPer + k);
-        const uint4 e = *(hit.rec ? hit.rec : g_regular);
+        const uint4 e = table[idx];
         gx[k] = e.x;
         gy[k] = e.y;
         gz[k] = e.z;
         gw[k] = e.w;
-        fw[k] = hit.rec ? hit.flags[hit.idx >> 5] : 0u;
-        fbit |= (hit.idx & 31u) << (5 * k);
+        fw[k] = table_flags(table)[idx >> 5];
+        fbit |= (idx & 31u) << (5 * k);
     }
 #pragma unroll
     for (int k = 0; k < kPer; ++k) {
@@ -871,6 +937,18 @@ __device__ __forceinline__ void gradient_tile(const void *__restrict__ field, co
     }
 }
 
+// Column order: tile t of a box of bxc x (any) x nz tiles, in 32-bit divisions
+// (a launch has fewer than 2^31 tiles, a side fewer than 2^31 vertices).
+struct TileAt {
+    uint32_t x, y, z;
+};
+
+__device__ __forceinline__ TileAt tile_at(uint32_t t, uint32_t nz, uint32_t bxc)
+{
+    const uint32_t col = t / nz, by = col / bxc;
+    return TileAt{col - by * bxc, by, t - col * nz};
+}
+
 // Keys: RankKeys reads the int32 order; F32Keys / F64Keys read the values
 // (flags receives DMS_FLAG_NAN for a NaN among them).
 // Tiles in column order, z fastest: the tiles running at the same time then
@@ -878,16 +956,16 @@ __device__ __forceinline__ void gradient_tile(const void *__restrict__ field, co
 // three halo planes, so most halo reads hit a cache (row order, with z
 // slowest, put those neighbours a whole plane of tiles apart).
 template <typename Keys, int GX, int GY>
-__global__ __launch_bounds__(kThreads, 8) void k_gradient(const void *__restrict__ field, Box B, int64_t bx_count,
+__global__ __launch_bounds__(kThreads, 8) void k_gradient(const void *__restrict__ field, Box B, uint32_t bx_count,
                                                           uint4 *__restrict__ rec,
-                                                          const uint4 *__restrict__ defect8, Handoff H,
+                                                          const uint4 *__restrict__ table, Handoff H,
                                                           uint32_t *flags, uint32_t *__restrict__ mark)
 {
     __shared__ TileShared sh;
     __shared__ typename Keys::H tile[Tile<GX, GY>::kHalo];
-    const int64_t t = blockIdx.x;
-    const int64_t bz = t % B.w2, col = t / B.w2, bx = col % bx_count, by = col / bx_count;
-    gradient_tile<Keys, GX, GY>(field, B, bx, by, bz, blockIdx.x, rec, defect8, H, flags, mark, sh, tile);
+    const TileAt T = tile_at(blockIdx.x, (uint32_t)B.w2, bx_count);
+    const int64_t bx = T.x, by = T.y, bz = T.z;
+    gradient_tile<Keys, GX, GY>(field, B, bx, by, bz, blockIdx.x, rec, table, H, flags, mark, sh, tile);
 }
 
 // Batched form: many whole fields, concatenated; one block per tile of the
@@ -907,26 +985,25 @@ __device__ __forceinline__ Box batch_box(const BatchTiles &L, int64_t t, int64_t
 {
     const int f = L.tile_field[t];
     const BatchField F = L.fields[f];
-    const int64_t bxc = (F.n[0] + GX - 1) / GX;
     // column order inside the field, as in k_gradient
-    const int64_t k = t - L.tile_start[f], col = k / F.n[2];
-    bz = k % F.n[2];
-    bx = col % bxc;
-    by = col / bxc;
+    const TileAt T = tile_at((uint32_t)(t - L.tile_start[f]), (uint32_t)F.n[2], (uint32_t)((F.n[0] + GX - 1) / GX));
+    bx = T.x;
+    by = T.y;
+    bz = T.z;
     return Box{F.n[0], F.n[1], F.n[2], 0, 0, 0, F.n[0], F.n[1], F.n[2], F.off};
 }
 
 template <int GX, int GY>
 __global__ __launch_bounds__(kThreads, 8) void k_gradient_batch(const int32_t *__restrict__ order, BatchTiles L,
                                                                 uint4 *__restrict__ rec,
-                                                                const uint4 *__restrict__ defect8, Handoff H,
+                                                                const uint4 *__restrict__ table, Handoff H,
                                                                 uint32_t *__restrict__ mark)
 {
     __shared__ TileShared sh;
     __shared__ int32_t tile[Tile<GX, GY>::kHalo];
     int64_t bx, by, bz;
     const Box B = batch_box<GX, GY>(L, blockIdx.x, bx, by, bz);
-    gradient_tile<RankKeys, GX, GY>(order + B.rec_off, B, bx, by, bz, blockIdx.x, rec, defect8, H, nullptr, mark, sh,
+    gradient_tile<RankKeys, GX, GY>(order + B.rec_off, B, bx, by, bz, blockIdx.x, rec, table, H, nullptr, mark, sh,
                                     tile);
 }
 
@@ -969,7 +1046,7 @@ __device__ __forceinline__ void dense_tile(const void *__restrict__ field, const
         const uint32_t low = lower_mask(o, ox);
         const bool gen = general_vertex(low);
         if (k == 0) skip = skip_tables(in, gen);
-        if (mine && in && (gen || whole || (k > 0 && skip))) {
+        if (mine && in && (gen || whole || skip)) {
             const uint32_t m = (uint32_t)__popc(low);
             sizes |= (128u | m) << (8 * k);
             atomicAdd(&sh.bins[m], 1u);
@@ -1041,7 +1118,7 @@ __device__ __forceinline__ void dense_walk(const Handoff &H, uint32_t ntiles, So
 // 13 + 18 + 20 us on a 24 x 20 x 16 noise field, this kernel alone 20.
 template <typename Keys, int GX, int GY>
 __global__ __launch_bounds__(kThreads, 6) void k_gradient_dense(const void *__restrict__ field, Box B,
-                                                                int64_t bx_count, uint32_t ntiles, bool whole,
+                                                                uint32_t bx_count, uint32_t ntiles, bool whole,
                                                                 uint4 *__restrict__ rec, Handoff H, uint32_t *flags,
                                                                 uint32_t *__restrict__ mark)
 {
@@ -1049,7 +1126,8 @@ __global__ __launch_bounds__(kThreads, 6) void k_gradient_dense(const void *__re
     __shared__ typename Keys::H tile[Tile<GX, GY>::kHalo];
     load_tables(sh.T);
     dense_walk(H, ntiles, [&](uint32_t t, int part, int parts) {
-        const int64_t bz = t % B.w2, col = t / B.w2, bx = col % bx_count, by = col / bx_count;
+        const TileAt T = tile_at(t, (uint32_t)B.w2, bx_count);
+        const int64_t bx = T.x, by = T.y, bz = T.z;
         dense_tile<Keys, GX, GY>(field, B, bx, by, bz, part, parts, whole, rec, flags, mark, sh, tile);
     });
 }
@@ -1144,7 +1222,7 @@ __device__ void lehmer_decode(uint32_t code, uint32_t *rank)
 // Fills the regular-vertex table: entry side * 5040 + code holds the record of
 // the configuration whose lower neighbours are, for pair i, neighbour i or
 // 13 - i (bit i of side), ordered by the permutation with Lehmer code `code`.
-__global__ __launch_bounds__(kThreads) void k_regular_table()
+__global__ __launch_bounds__(kThreads) void k_regular_table(uint4 *__restrict__ table)
 {
     __shared__ StarTables T;
     load_tables(T);
@@ -1163,12 +1241,13 @@ __global__ __launch_bounds__(kThreads) void k_regular_table()
         }
         uint4 r;
         crit = process_vertex<RankKeys>(o, 50, T, r);
-        g_regular[idx] = r;
+        table[idx] = r;
     }
     const uint64_t m = __ballot(crit);
     if (lane_id() == 0 && idx < kRegular) {
-        g_regular_flags[idx / 32] = (uint32_t)m;
-        g_regular_flags[idx / 32 + 1] = (uint32_t)(m >> 32);
+        uint32_t *flags = (uint32_t *)(table + kEntries);
+        flags[idx / 32] = (uint32_t)m;
+        flags[idx / 32 + 1] = (uint32_t)(m >> 32);
     }
 }
 
@@ -1177,7 +1256,7 @@ __global__ __launch_bounds__(kThreads) void k_regular_table()
 // slots where slot j (pair j, wholly upper) ranks above the other six --
 // entries whose code puts it elsewhere are never read and stay zero.
 template <bool kEight>
-__global__ __launch_bounds__(kThreads) void k_defect_table(uint4 *table)
+__global__ __launch_bounds__(kThreads) void k_defect_table(uint4 *__restrict__ table)
 {
     __shared__ StarTables T;
     load_tables(T);
@@ -1185,7 +1264,8 @@ __global__ __launch_bounds__(kThreads) void k_defect_table(uint4 *table)
     constexpr int N = kEight ? 8 : 7;
     constexpr int64_t perms = kEight ? kPerm8 : kPerm7;
     constexpr int64_t total = 7 * 64 * perms;
-    uint32_t *flags = kEight ? g_defect8_flags : g_defect6_flags;
+    constexpr uint32_t first = kEight ? kFirst8 : kFirst6;
+    uint32_t *flags = (uint32_t *)(table + kEntries) + first / 32;
     const int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x;  // a wave covers 64 aligned entries
     bool crit = false;
     if (idx < total) {
@@ -1208,7 +1288,7 @@ __global__ __launch_bounds__(kThreads) void k_defect_table(uint4 *table)
             if (kEight) o[j] = (int32_t)rank[7];
             crit = process_vertex<RankKeys>(o, 50, T, r);
         }
-        table[idx] = r;
+        table[first + idx] = r;
     }
     const uint64_t m = __ballot(crit);
     if (lane_id() == 0 && idx < total) {
@@ -1225,7 +1305,7 @@ namespace dms {
 namespace {
 std::atomic<uint64_t> g_regular_ready{0};  // one bit per device that holds the tables
 std::mutex g_table_mutex;
-uint4 *g_defect8_ptr[64];  // per device, held until the process ends
+uint4 *g_table_ptr[64];  // per device, held until the process ends
 }
 
 int init_tables(hipStream_t s)
@@ -1237,29 +1317,26 @@ int init_tables(hipStream_t s)
     if (g_regular_ready.load() & bit) return DMS_OK;
     std::lock_guard<std::mutex> lock(g_table_mutex);
     if (g_regular_ready.load() & bit) return DMS_OK;
-    if (!g_defect8_ptr[dev]) {
+    if (!g_table_ptr[dev]) {
         void *p = nullptr;
-        if (hipMalloc(&p, (size_t)kDefect8 * sizeof(uint4)) != hipSuccess) return DMS_E_HIP;
-        g_defect8_ptr[dev] = (uint4 *)p;
+        if (hipMalloc(&p, kTableBytes) != hipSuccess) return DMS_E_HIP;
+        g_table_ptr[dev] = (uint4 *)p;
     }
-    uint4 *d6 = nullptr;
-    if (hipGetSymbolAddress((void **)&d6, HIP_SYMBOL(g_defect6)) != hipSuccess) return DMS_E_HIP;
-    hipLaunchKernelGGL(k_regular_table, dim3((kRegular + kThreads - 1) / kThreads), dim3(kThreads), 0, s);
-    hipLaunchKernelGGL(k_defect_table<false>, dim3((kDefect6 + kThreads - 1) / kThreads), dim3(kThreads),
-                       0, s, d6);
-    hipLaunchKernelGGL(k_defect_table<true>, dim3((unsigned)((kDefect8 + kThreads - 1) / kThreads)),
-                       dim3(kThreads), 0, s, g_defect8_ptr[dev]);
+    uint4 *table = g_table_ptr[dev];
+    hipLaunchKernelGGL(k_regular_table, dim3((kRegular + kThreads - 1) / kThreads), dim3(kThreads), 0, s, table);
+    hipLaunchKernelGGL(k_defect_table<false>, dim3((kDefect6 + kThreads - 1) / kThreads), dim3(kThreads), 0, s, table);
+    hipLaunchKernelGGL(k_defect_table<true>, dim3((kDefect8 + kThreads - 1) / kThreads), dim3(kThreads), 0, s, table);
     if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) return DMS_E_HIP;
     g_regular_ready.fetch_or(bit);
     return DMS_OK;
 }
 
-// The current device's |L| = 8 table (null before init_tables).
-static const uint4 *defect8_table()
+// The current device's tables (null before init_tables).
+static const uint4 *device_tables()
 {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return nullptr;
-    return (g_regular_ready.load() >> dev) & 1u ? g_defect8_ptr[dev] : nullptr;
+    return (g_regular_ready.load() >> dev) & 1u ? g_table_ptr[dev] : nullptr;
 }
 
 // DMS_OK when the current device is a gfx950 whose tables init_tables has
@@ -1267,7 +1344,7 @@ static const uint4 *defect8_table()
 int tables_ready()
 {
     if (const int dc = device_check()) return dc;
-    return defect8_table() ? DMS_OK : DMS_E_NOT_INITIALISED;
+    return device_tables() ? DMS_OK : DMS_E_NOT_INITIALISED;
 }
 
 
@@ -1335,10 +1412,10 @@ static int launch_gradient_keys(const void *field, const int64_t *dims, const in
     const Handoff H = handoff_carve(whole ? nullptr : ws, owned);
     gradient_begin(mark, owned, H, s);
     if (!whole)
-        hipLaunchKernelGGL((k_gradient<Keys, kGX, kGY>), dim3((unsigned)blocks), dim3(kThreads), 0, s, field, B, bxc,
-                           (uint4 *)rec, defect8_table(), H, flags, mark);
+        hipLaunchKernelGGL((k_gradient<Keys, kGX, kGY>), dim3((unsigned)blocks), dim3(kThreads), 0, s, field, B, (uint32_t)bxc,
+                           (uint4 *)rec, device_tables(), H, flags, mark);
     hipLaunchKernelGGL((k_gradient_dense<Keys, kGX, kGY>), dim3(dense_blocks(blocks)), dim3(kThreads), 0, s, field,
-                       B, bxc, (uint32_t)blocks, whole, (uint4 *)rec, H, whole ? flags : nullptr, mark);
+                       B, (uint32_t)bxc, (uint32_t)blocks, whole, (uint4 *)rec, H, whole ? flags : nullptr, mark);
     queue_finish(H, rec, mark, s);
     return launch_status();
 }
@@ -1350,7 +1427,7 @@ int launch_gradient_batch(int variant, const int32_t *order, const BatchField *f
     (void)nfields;
     if (total_tiles == 0) return DMS_OK;
     if (total_tiles > 2147483647LL) return DMS_E_SIZE;
-    const uint4 *d8 = defect8_table();
+    const uint4 *table = device_tables();
     const bool whole = total_tiles <= kWholeTiles;
     const Handoff H = handoff_carve(whole ? nullptr : ws, total_verts);
     gradient_begin(mark, total_verts, H, s);
@@ -1358,7 +1435,7 @@ int launch_gradient_batch(int variant, const int32_t *order, const BatchField *f
 #define DMS_LAUNCH(GXV)                                                                                             \
     if (!whole)                                                                                                      \
         hipLaunchKernelGGL((k_gradient_batch<GXV, kTileVerts / GXV>), dim3((unsigned)total_tiles), dim3(kThreads),   \
-                           0, s, order, L, (uint4 *)rec, d8, H, mark);                                               \
+                           0, s, order, L, (uint4 *)rec, table, H, mark);                                               \
     hipLaunchKernelGGL((k_gradient_dense_batch<GXV, kTileVerts / GXV>), dim3(dense_blocks(total_tiles)),             \
                        dim3(kThreads), 0, s, order, L, (uint32_t)total_tiles, whole, (uint4 *)rec, H, mark)
     switch (variant) {

@@ -596,18 +596,19 @@ __device__ __forceinline__ uint32_t table_entry(uint32_t low, const C *o)
 #pragma unroll
     for (int i = 0; i < 7; ++i) {
         const C a = o[i], b = o[13 - i];
-        const uint32_t w = (uint32_t)((int32_t)(both << (31 - i)) >> 31);
+        const uint32_t w = (uint32_t)__builtin_amdgcn_sbfe((int)both, i, 1);  // all ones or zeros
         v[i] = pick(w, b, cmin(a, b));
         v[7] = cmin(v[7], pick(w, a, kHigh));
     }
     uint32_t l[7];
     lehmer_digits(v, l);
-    // factorial sums of the digits, by Horner's rule
+    // factorial sums of the digits, by Horner's rule (in 24-bit products: the
+    // full 32-bit multiply-add is four times slower)
     uint32_t code7 = l[0], code8 = l[0];
 #pragma unroll
     for (int i = 1; i < 7; ++i) {
-        code7 = code7 * (uint32_t)(7 - i) + l[i];
-        code8 = code8 * (uint32_t)(8 - i) + l[i];
+        code7 = __umul24(code7, (uint32_t)(7 - i)) + l[i];
+        code8 = __umul24(code8, (uint32_t)(8 - i)) + l[i];
     }
     const bool eight = both != 0, regular = one == 0x7fu;
     const uint32_t j = (uint32_t)__builtin_ctz(~one | 0x80u);  // (7 for a regular vertex)
@@ -615,6 +616,15 @@ __device__ __forceinline__ uint32_t table_entry(uint32_t low, const C *o)
     const uint32_t group = regular ? side : j * 64u + side6;
     const uint32_t first = eight ? kFirst8 : regular ? 0u : kFirst6;
     return __umul24(group, eight ? (uint32_t)kPerm8 : (uint32_t)kPerm7) + (eight ? code8 : code7) + first;
+}
+
+// Stores a row's record past the L2's ordinary replacement: a tile's 16 KB of
+// records are not read again here, the halo planes it shares with the tiles
+// above are.  (A 1026^3 gradient, 17 GB of records: 11.3 ms with ordinary
+// stores, 10.2 ms so; 512^3: 3.52 and 3.50.)
+__device__ __forceinline__ void store_record(uint4 *p, uint32_t x, uint32_t y, uint32_t z, uint32_t w) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    __builtin_nontemporal_store(u32x4{x, y, z, w}, (u32x4 *)p);
 }
 
 template <int GX, int GY>
@@ -738,34 +748,43 @@ __device__ __forceinline__ void stage_halo(const void *__restrict__ field, const
     bool nan = false, nan_any = false;
     bool staged = false;  // uniform
     if constexpr (GX == kWave) {
-      if (full) {
-        // inside the grid, rows of 66 orders: wave w loads rows w, w + 4, ...
-        // (64 consecutive orders from a row base computed in scalar
-        // registers, so the loads need no per-lane address arithmetic), and
-        // the first 2 x 54 threads load the rows' last two orders; every
-        // load is issued before any LDS store
+      using H = typename Keys::H;
+      // inside the grid, and the tile's three planes within 32-bit byte
+      // offsets of its first value
+      if (full && (2 * nx * ny + S::HY * nx) * (int64_t)sizeof(H) < (1ll << 32)) {
+        // rows of 66 values: wave w loads rows w, w + 4, ... (64 consecutive
+        // values from a row address kept in scalar registers), and the first
+        // 2 x 54 threads load the rows' last two values; every load is issued
+        // before any LDS store.  A row's offset is its number times the row
+        // stride, plus the rest of a plane for each plane before it; which
+        // planes those are is known at compile time for all but one row.
+        // (With each row's plane, line and 64-bit address computed from its
+        // number the staging took 405 of the kernel's 670 scalar instructions
+        // a wave.)
         constexpr int kRows = S::HY * S::HZ;
         constexpr int kWavesB = kThreads / kWave;
         constexpr int kPerRow = (kRows + kWavesB - 1) / kWavesB;
-        static_assert(S::HX == kWave + 2 && 2 * kRows <= kThreads, "row split");
-        const int wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave;
-        const int64_t base0 = x0 + nx * (y0 + ny * z0), pstride = nx * ny;
-        typename Keys::H hv[kPerRow];
+        static_assert(S::HX == kWave + 2 && 2 * kRows <= kThreads && kWavesB == 4 && S::HZ == 3, "row split");
+        const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid / kWave) & 3u, lane = (uint32_t)tid % kWave;
+        const char *first = (const char *)field + (x0 + nx * (y0 + ny * z0)) * (int64_t)sizeof(H);
+        const uint32_t line = (uint32_t)nx * (uint32_t)sizeof(H);
+        const uint32_t skip = (uint32_t)((ny - S::HY) * nx) * (uint32_t)sizeof(H);  // from a plane's rows to the next's
+        H hv[kPerRow];
 #pragma unroll
         for (int k = 0; k < kPerRow; ++k) {
-            const int r = min(wave + kWavesB * k, kRows - 1);
-            const int hz = r / S::HY, hy = r - hz * S::HY;
-            hv[k] = Keys::load(field, base0 + hz * pstride + hy * nx + lane, nan);
+            const uint32_t r = min(wave + (uint32_t)(kWavesB * k), (uint32_t)kRows - 1u);
+            const char *row = first + (r * line + (r >= S::HY ? skip : 0u) + (r >= 2 * S::HY ? skip : 0u));
+            hv[k] = Keys::load(row, lane, nan);
             nan_any |= nan;
         }
-        const int er = tid < 2 * kRows ? tid >> 1 : 0;
-        const int ez = er / S::HY, ey = er - ez * S::HY;
-        const typename Keys::H ev = Keys::load(field, base0 + ez * pstride + ey * nx + kWave + (tid & 1), nan);
+        const uint32_t er = tid < 2 * kRows ? (uint32_t)tid >> 1 : 0u;
+        const uint32_t eo = er * line + (er >= S::HY ? skip : 0u) + (er >= 2 * S::HY ? skip : 0u);
+        const H ev = Keys::load(first + eo, kWave + (tid & 1), nan);
         nan_any |= nan;
 #pragma unroll
         for (int k = 0; k < kPerRow; ++k) {
-            const int r = wave + kWavesB * k;
-            if (r < kRows) tile[r * S::HX + lane] = hv[k];
+            const uint32_t r = wave + (uint32_t)(kWavesB * k);
+            if (r < (uint32_t)kRows) tile[r * S::HX + lane] = hv[k];
         }
         if (tid < 2 * kRows) tile[er * S::HX + kWave + (tid & 1)] = ev;
         staged = true;
@@ -826,6 +845,16 @@ __device__ __forceinline__ bool skip_tables(bool in, bool gen)
 // a box: their records from the precomputed tables.  The other vertices are
 // handed over (Handoff).  tile_no: the tile's number in the launch.  Must be
 // entered by the whole block.
+//
+// Bound by the record stores (16 B a vertex; a copy of the kernel without
+// them takes half the time, one without table and flag reads five sixths),
+// then by the latency of staging, table read and store one after the other:
+// the vector work alone is a quarter.  So the three table families lie behind
+// one 32-bit entry number (no branch or pointer per family), masks and digits
+// are built from borrow and carry bits, and a row's loads have scalar
+// addresses.  With a pointer, a branch and a loop per family, 1026^3 / 512^3 of
+// ranks and 512^3 of float values took 11.6 / 5.0 / 4.7 ms; now
+// 10.2 / 3.5 / 3.0 ms with the general vertices' kernels.
 struct TileShared {
     uint32_t qbase, nlist;
     uint16_t list[kTileVerts];  // general vertices of the tile (tile positions)
@@ -895,7 +924,7 @@ __device__ __forceinline__ void gradient_tile(const void *__restrict__ field, co
         const int ty = GX == kWave ? wave_u + (kThreads / kWave) * k : v / GX;
         if ((state >> (kPer + k)) & 1u) {
             const int64_t r = rbase + tx + w0 * ty;
-            rec[r] = make_uint4(gx[k], gy[k], gz[k], gw[k]);
+            store_record(rec + r, gx[k], gy[k], gz[k], gw[k]);
             if (mark && ((fw[k] >> ((fbit >> (5 * k)) & 31u)) & 1u)) mark_critical(mark, r);
         } else {
             sh.list[atomicAdd(&sh.nlist, 1u)] = (uint16_t)v;

@@ -91,19 +91,28 @@ __device__ __forceinline__ uint64_t key_of(double v, bool &nan)
 }
 
 // Lanes of the wave (among `active`) holding the same 8-bit digit as this
-// lane: intersect, bit by bit, the ballot of lanes agreeing with it.
+// lane: intersect, bit by bit, the ballot of lanes agreeing with it (four
+// instructions a bit: the bit spread over a word, its ballot, and an
+// and-xnor for each half of the mask).
 __device__ __forceinline__ uint64_t match_digit8(uint32_t d, uint64_t active)
 {
-    uint64_t peers = active;
+    uint32_t lo = (uint32_t)active, hi = (uint32_t)(active >> 32);
 #pragma unroll
     for (int b = 0; b < 8; ++b) {
-        const bool bit = (d >> b) & 1u;
-        const uint64_t bal = __ballot(bit);
-        peers &= bit ? bal : ~bal;
+        const uint32_t m = (uint32_t)__builtin_amdgcn_sbfe((int)d, b, 1);  // the lane's bit, in all bits
+        const uint64_t bal = __ballot(m != 0u);
+        lo = __builtin_amdgcn_bitop3_b32(lo, (uint32_t)bal, m, 0x90);  // lo & ~(bal ^ m)
+        hi = __builtin_amdgcn_bitop3_b32(hi, (uint32_t)(bal >> 32), m, 0x90);
     }
-    return peers;
+    return (uint64_t)hi << 32 | lo;
 }
 
 __device__ __forceinline__ uint64_t lanemask_lt() { return (1ull << lane_id()) - 1ull; }
+
+// Set bits of mask below this lane.
+__device__ __forceinline__ uint32_t lanes_below(uint64_t mask)
+{
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
 
 }  // namespace dms

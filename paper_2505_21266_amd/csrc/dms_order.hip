@@ -133,9 +133,10 @@ __device__ __forceinline__ uint32_t settled(uint32_t v)
 
 // Element k of this lane in its tile (wave-striped), as an offset from the
 // tile's first element.
+template <int kIt = kItems>
 __device__ __forceinline__ int local_index(int wave, int k, int lane)
 {
-    return wave * (kItems * kWave) + k * kWave + lane;
+    return wave * (kIt * kWave) + k * kWave + lane;
 }
 
 template <int kT = kTile>
@@ -195,10 +196,14 @@ __device__ __forceinline__ int64_t item_at(int64_t t0, int li, int last)
 
 // (1) per-tile histogram of the digit at `shift`; counts is digit-major:
 // counts[d * ntiles + tile].
-// ids: the vertex ids, read by the field pass of a batch, whose digit is
-// each id's field.
 // kField (the last pass of a batch with 4-byte keys): the digit is the field
-// of the vertex id instead of a byte of the key.
+// of the vertex id (ids) instead of a byte of the key.
+//
+// The order of the items does not matter here: a whole tile is read 16 bytes
+// a lane, and its items need no tests.  Bound by the loads for 4-byte keys
+// (1.08e9 of them 0.88 ms, 4.9 TB/s) and by the LDS atomics for 2- and 1-byte
+// keys: 0.61 and 0.56 ms with an item a load and a test of each item, 0.49 and
+// 0.43 so.
 template <typename V, typename K, bool kFirst, int kThr, bool kField = false>
 __global__ __launch_bounds__(kThr) void k_tile_hist(const void *src, int64_t n, int shift,
                                                         uint32_t *counts, int64_t ntiles,
@@ -215,37 +220,59 @@ __global__ __launch_bounds__(kThr) void k_tile_hist(const void *src, int64_t n, 
     if (count == 0) return;  // block-uniform
     const int last = count - 1;
     using R = SrcT<V, K, kFirst>;
-    R raw[kItems];
-    uint32_t bid[kItems];
-#pragma unroll
-    for (int k = 0; k < kItems; ++k)
-        if constexpr (!kField) raw[k] = ((const R *)src)[item_at(t0, local_index(wave, k, lane), last)];
-    if (ids) {
-#pragma unroll
-        for (int k = 0; k < kItems; ++k) bid[k] = ids[item_at(t0, local_index(wave, k, lane), last)];
-    }
-    for (int i = tid; i < kCopies * (kRadix + 1); i += kThr) (&hist[0][0])[i] = 0;
-    if constexpr (kField) load_field_offsets(fo, foff, nfields);
-    __syncthreads();
-    const int fsh = kField ? field_table_shift(n) : 0;
+    const auto zero = [&] {
+        for (int i = tid; i < kCopies * (kRadix + 1); i += kThr) (&hist[0][0])[i] = 0;
+    };
+    bool nan_any = false;
+    const auto digit = [&](R r, bool valid) {
+        bool nan;
+        const K key = to_key<V, K, kFirst>(r, nan);
+        nan_any |= valid && nan;
+        return (uint32_t)(key >> shift) & (kRadix - 1);
+    };
+    constexpr int kPer = 16 / (int)sizeof(R), kVecs = kItems / kPer;
+    // (uniform; the caller's values may be aligned to their own size only)
+    const bool whole = !kField && count == kThr * kItems && ((uintptr_t)src & 15u) == 0;
     if constexpr (kField) {
+        uint32_t id[kItems];
+#pragma unroll
+        for (int k = 0; k < kItems; ++k) id[k] = ids[item_at(t0, local_index(wave, k, lane), last)];
+        zero();
+        load_field_offsets(fo, foff, nfields);
+        __syncthreads();
+        const int fsh = field_table_shift(n);
         build_field_table(ftab, fo, nfields, n, fsh);
         __syncthreads();
-    }
-    bool nan_any = false;
 #pragma unroll
-    for (int k = 0; k < kItems; ++k) {
-        const bool valid = local_index(wave, k, lane) < count;
-        uint32_t d;
-        if constexpr (kField) {
-            d = (uint32_t)field_by_table(ftab, fo, fsh, bid[k]);
-        } else {
-            bool nan;
-            const K key = to_key<V, K, kFirst>(raw[k], nan);
-            nan_any |= valid && nan;
-            d = (uint32_t)(key >> shift) & (kRadix - 1);
+        for (int k = 0; k < kItems; ++k)
+            hist_add(hist, (uint32_t)field_by_table(ftab, fo, fsh, id[k]), local_index(wave, k, lane) < count);
+    } else if (whole) {
+        struct alignas(16) Vec {
+            R r[kPer];
+        };
+        const uint4 *at = (const uint4 *)((const R *)src + t0);
+        uint4 w[kVecs];
+#pragma unroll
+        for (int c = 0; c < kVecs; ++c) w[c] = at[c * kThr + tid];
+        zero();
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < kVecs; ++c) {
+            const Vec v = __builtin_bit_cast(Vec, w[c]);
+#pragma unroll
+            for (int j = 0; j < kPer; ++j) atomicAdd(&hist[lane & (kCopies - 1)][digit(v.r[j], true)], 1u);
         }
-        hist_add(hist, d, valid);
+    } else {
+        R raw[kItems];
+#pragma unroll
+        for (int k = 0; k < kItems; ++k) raw[k] = ((const R *)src)[item_at(t0, local_index(wave, k, lane), last)];
+        zero();
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kItems; ++k) {
+            const bool valid = local_index(wave, k, lane) < count;
+            hist_add(hist, digit(raw[k], valid), valid);
+        }
     }
     __syncthreads();
     if (kFirst && __ballot(nan_any) && lane == 0) atomicOr(flags, (uint32_t)DMS_FLAG_NAN);
@@ -292,7 +319,9 @@ __device__ __forceinline__ uint32_t wave_rank(uint32_t d, bool valid, CT *wh, ui
     }
     uint32_t base = 0;
     if (valid) base = wh[d];
-    const uint32_t below = (uint32_t)__popcll(peers & lanemask_lt());
+    // (with the lane counter below the LDS masks the scatters of 8-byte keys
+    // take 0.87 ms for 2^27 instead of 0.75)
+    const uint32_t below = kLds ? (uint32_t)__popcll(peers & lanemask_lt()) : lanes_below(peers);
     if (valid && below == 0) wh[d] = (CT)(base + (uint32_t)__popcll(peers));
     return base + below;
 }
@@ -516,6 +545,11 @@ InvertPlan invert_plan(int64_t n)
     return P;
 }
 
+// An (id, position) pair: one word, so that a run of pairs is one range of
+// memory.
+__device__ __forceinline__ uint64_t pair_of(uint32_t id, int32_t pos) { return (uint64_t)(uint32_t)pos << 32 | id; }
+__device__ __forceinline__ int32_t pair_pos(uint64_t p) { return (int32_t)(p >> 32); }
+
 // Level 0: the last radix pass.  Each item's final position g comes from the
 // digit ranks as in k_scatter; the tile is then re-ranked by coarse bucket
 // and staged in LDS in bucket order, so that a bucket's pairs from this tile
@@ -525,16 +559,18 @@ InvertPlan invert_plan(int64_t n)
 // matter to the inversion, which places them by id, and bucket b starts at
 // position b << bshift because the ids are a permutation.
 // For batches the position is taken relative to the field's first vertex.
-// Per-wave counts are 16-bit (at most a tile), so that the block's LDS stays
-// just under 40 KiB at 256 threads (four blocks per CU) and 75 KiB at 512
-// (two).
+// Bound by vector instructions (the ballots of the digit) and then by the
+// scattered stores: 1.08e9 keys took 4.45 ms with the ids and positions in two
+// arrays, a run of 128 bytes in each, and the digit matched by six
+// instructions a bit; 4.34 ms with pairs, 3.86 with four instructions a bit,
+// 3.72 without tests in whole tiles (13 bytes a key: 3.8 TB/s).
 template <typename K, int kThr, bool kField = false>
 __global__ __launch_bounds__(kThr) void k_scatter_last(const K *src, const uint32_t *src_ids,
                                                            int64_t n, int shift,
                                                            const uint32_t *offsets,
                                                            uint32_t *bfill, int64_t ntiles,
                                                            const int64_t *foff, int nfields, int bshift,
-                                                           uint32_t *pair_id, int32_t *pair_pos)
+                                                           uint64_t *pairs)
 {
     __shared__ int64_t fo[kField ? kFieldPassFields + 1 : 1];
     constexpr int kW = kThr / kWave, kT = kThr * kItems;
@@ -557,111 +593,116 @@ __global__ __launch_bounds__(kThr) void k_scatter_last(const K *src, const uint3
     const int64_t t0 = tile * kT;
     const int count = tile_count<kT>(n, tile);
     if (count == 0) return;  // block-uniform
-    // per item after the ranking: the id and, packed, its digit rank inside
-    // the wave (below 16 x 64 = 2^10), its digit and its slot among the
-    // tile's pairs of its bucket (below 2^13); batches of 8-byte keys also
-    // keep the field.
-    // The digit ranks must be stable (they give the sorted position); the
-    // bucket slots need not be (the inversion places pairs by id), so they
-    // come from one LDS atomic per item.
-    uint32_t id[kItems], pk[kItems];
-    uint32_t fld[sizeof(K) == 8 ? kItems : 1];
-    {
-        K key[kItems];
+    // all: the tile is whole, and its items need no tests
+    const auto tile_pairs = [&](auto all) {
+        constexpr bool whole = decltype(all)::value;
+        // per item after the ranking: the id and, packed, its digit rank inside
+        // the wave (below 16 x 64 = 2^10), its digit and its slot among the
+        // tile's pairs of its bucket (below 2^13); batches of 8-byte keys also
+        // keep the field.
+        // The digit ranks must be stable (they give the sorted position); the
+        // bucket slots need not be (the inversion places pairs by id), so they
+        // come from one LDS atomic per item.
+        uint32_t id[kItems], pk[kItems];
+        uint32_t fld[sizeof(K) == 8 ? kItems : 1];
+        {
+            K key[kItems];
 #pragma unroll
-        for (int k = 0; k < kItems; ++k) {
-            const int64_t at = item_at(t0, local_index(wave, k, lane), count - 1);
-            if constexpr (!kField) key[k] = src[at];  // the field pass needs only the ids
-            id[k] = src_ids[at];
-        }
-        // the field table lives in the staging bytes, unused until the
-        // ranking's barrier (the ranking matches by ballots, without the
-        // LDS masks)
-        const int fsh = kField ? field_table_shift(n) : 0;
-        if constexpr (kField) {
-            build_field_table(S.ftab, fo, nfields, n, fsh);
-            __syncthreads();
-        }
-#pragma unroll
-        for (int k = 0; k < kItems; ++k) {
-            const bool valid = local_index(wave, k, lane) < count;
-            uint32_t d;
-            if constexpr (kField)
-                d = (uint32_t)field_by_table(S.ftab, fo, fsh, id[k]);
-            else
-                d = (uint32_t)(key[k] >> shift) & (kRadix - 1);
-            // the top byte (sign and exponent) takes few values, and a tile
-            // spans few fields: ballots match it faster than the LDS masks,
-            // which serve the random id buckets
-            const uint32_t rd = wave_rank<false>(d, valid, dwh[wave], S.mk[wave]);
-            const uint32_t rb = valid ? atomicAdd(&bcnt[(id[k] >> bshift) & (kRadix - 1)], 1u) : 0u;
-            // settled here: otherwise the compiler sinks the rank popcounts past
-            // the barrier and keeps every item's two 64-bit lane masks alive
-            pk[k] = settled(rd | d << 10 | rb << 18);
-            if constexpr (!kField && sizeof(K) == 8) fld[k] = (uint32_t)(key[k] >> 32);
-        }
-    }
-    __syncthreads();
-    {
-        wave_prefix<kThr>(dwh);
-        uint32_t total;
-        const uint32_t nb = tid < kRadix ? bcnt[tid] : 0u;  // the tile's pairs of bucket tid
-        const uint32_t start = block_exclusive_scan<uint32_t, kThr>(nb, &total);
-        if (tid < kRadix) {
-            bstart[tid] = start;
-            uint32_t gb = offsets[(int64_t)tid * ntiles + tile];
-            if constexpr (kField) gb -= tid <= nfields ? (uint32_t)fo[tid] : 0u;  // the digit is the field
-#pragma unroll
-            for (int w = 0; w < kW; ++w) dwh[w][tid] += gb;
-            bbase[tid] = nb ? ((uint32_t)tid << bshift) + atomicAdd(&bfill[tid], nb) - start : 0u;
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < kItems; ++k) {
-        if (local_index(wave, k, lane) < count) {
-            const uint32_t d = (pk[k] >> 10) & (kRadix - 1);
-            const uint32_t b = (id[k] >> bshift) & (kRadix - 1);
-            int64_t g = (int64_t)(dwh[wave][d] + (pk[k] & 1023u));
-            if constexpr (!kField && sizeof(K) == 8) {
-                if (foff) g -= foff[fld[k]];
+            for (int k = 0; k < kItems; ++k) {
+                const int li = local_index(wave, k, lane);
+                const int64_t at = whole ? t0 + li : item_at(t0, li, count - 1);
+                if constexpr (!kField) key[k] = src[at];  // the field pass needs only the ids
+                id[k] = src_ids[at];
             }
-            const uint32_t pos = bstart[b] + (pk[k] >> 18);
-            if (pos < (uint32_t)kT) stage_put(S, pos, id[k], (int32_t)g);
-        }
-    }
-    __syncthreads();
+            // the field table lives in the staging bytes, unused until the
+            // ranking's barrier (the ranking matches by ballots, without the
+            // LDS masks)
+            const int fsh = kField ? field_table_shift(n) : 0;
+            if constexpr (kField) {
+                build_field_table(S.ftab, fo, nfields, n, fsh);
+                __syncthreads();
+            }
 #pragma unroll
-    for (int j = 0; j < kItems; ++j) {
-        const int p = tid + j * kThr;
-        if (p < count) {
-            uint32_t who;
-            int32_t at;
-            stage_get(S, p, who, at);
-            const uint32_t dst = bbase[(who >> bshift) & (kRadix - 1)] + (uint32_t)p;
-            if ((int64_t)dst < n) {
-                pair_id[dst] = who;
-                pair_pos[dst] = at;
+            for (int k = 0; k < kItems; ++k) {
+                const bool valid = whole || local_index(wave, k, lane) < count;
+                uint32_t d;
+                if constexpr (kField)
+                    d = (uint32_t)field_by_table(S.ftab, fo, fsh, id[k]);
+                else
+                    d = (uint32_t)(key[k] >> shift) & (kRadix - 1);
+                // the top byte (sign and exponent) takes few values, and a tile
+                // spans few fields: ballots match it faster than the LDS masks,
+                // which serve the random id buckets
+                const uint32_t rd = wave_rank<false>(d, valid, dwh[wave], S.mk[wave]);
+                const uint32_t rb = valid ? atomicAdd(&bcnt[(id[k] >> bshift) & (kRadix - 1)], 1u) : 0u;
+                // settled here: otherwise the compiler sinks the rank popcounts past
+                // the barrier and keeps every item's two 64-bit lane masks alive
+                pk[k] = settled(rd | d << 10 | rb << 18);
+                if constexpr (!kField && sizeof(K) == 8) fld[k] = (uint32_t)(key[k] >> 32);
             }
         }
-    }
+        __syncthreads();
+        {
+            wave_prefix<kThr>(dwh);
+            uint32_t total;
+            const uint32_t nb = tid < kRadix ? bcnt[tid] : 0u;  // the tile's pairs of bucket tid
+            const uint32_t start = block_exclusive_scan<uint32_t, kThr>(nb, &total);
+            if (tid < kRadix) {
+                bstart[tid] = start;
+                uint32_t gb = offsets[(int64_t)tid * ntiles + tile];
+                if constexpr (kField) gb -= tid <= nfields ? (uint32_t)fo[tid] : 0u;  // the digit is the field
+#pragma unroll
+                for (int w = 0; w < kW; ++w) dwh[w][tid] += gb;
+                bbase[tid] = nb ? ((uint32_t)tid << bshift) + atomicAdd(&bfill[tid], nb) - start : 0u;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kItems; ++k) {
+            if (whole || local_index(wave, k, lane) < count) {
+                const uint32_t d = (pk[k] >> 10) & (kRadix - 1);
+                const uint32_t b = (id[k] >> bshift) & (kRadix - 1);
+                int64_t g = (int64_t)(dwh[wave][d] + (pk[k] & 1023u));
+                if constexpr (!kField && sizeof(K) == 8) {
+                    if (foff) g -= foff[fld[k]];
+                }
+                const uint32_t pos = bstart[b] + (pk[k] >> 18);
+                if (pos < (uint32_t)kT) S.ab[pos] = pair_of(id[k], (int32_t)g);
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kItems; ++j) {
+            const int p = tid + j * kThr;
+            if (whole || p < count) {
+                const uint64_t pair = S.ab[p];
+                const uint32_t dst = bbase[((uint32_t)pair >> bshift) & (kRadix - 1)] + (uint32_t)p;
+                if ((int64_t)dst < n) pairs[dst] = pair;
+            }
+        }
+    };
+    if (count == kT) tile_pairs(std::true_type{});
+    else tile_pairs(std::false_type{});
 }
+
+constexpr int kFineThreads = 512;
+constexpr int kFineItems = kTile / kFineThreads;
+static_assert(kFineThreads >= kRadix, "a thread per window digit");
 
 // Level 1: a partition of each chunk of a coarse bucket by the fine digit
 // into the windows of ids.  As in level 0, a chunk's run for window w is
 // placed by one atomic add on the window's fill counter (wfill, zeroed
 // beforehand; window w starts at position w << fshift).  The ids are written
 // relative to their window (fshift <= 16 bits), 2 bytes instead of 4.
-__global__ __launch_bounds__(kThreads) void k_fine_scatter(const uint32_t *in_id, const int32_t *in_pos,
-                                                           int64_t n, int fshift, int flog, int qlog,
-                                                           int64_t nchunks, uint32_t *wfill,
-                                                           uint16_t *out_id, int32_t *out_pos)
+__global__ __launch_bounds__(kFineThreads) void k_fine_scatter(const uint64_t *__restrict__ pairs, int64_t n,
+                                                               int fshift, int flog, int qlog, int64_t nchunks,
+                                                               uint32_t *wfill, uint16_t *out_id,
+                                                               int32_t *out_pos)
 {
     __shared__ uint32_t cnt[kRadix];
     __shared__ uint32_t dstart[kRadix];
     __shared__ uint32_t gbase[kRadix];
-    __shared__ uint32_t sid[kTile];
-    __shared__ int32_t spos[kTile];
+    __shared__ uint64_t st[kTile];
 
     const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
     if (tid < kRadix) cnt[tid] = 0;
@@ -671,48 +712,46 @@ __global__ __launch_bounds__(kThreads) void k_fine_scatter(const uint32_t *in_id
     const int count = tile_count(n, c);
     if (count == 0) return;  // block-uniform
     const uint32_t fmask = (1u << flog) - 1u;
-    uint32_t id[kItems], slot[kItems];
-    int32_t pos[kItems];
+    uint64_t pair[kFineItems];
+    uint32_t slot[kFineItems];
 #pragma unroll
-    for (int k = 0; k < kItems; ++k) {  // unconditional loads (count >= 1)
-        const int64_t at = item_at(t0, local_index(wave, k, lane), count - 1);
-        id[k] = in_id[at];
-        pos[k] = in_pos[at];
-    }
+    for (int k = 0; k < kFineItems; ++k)  // unconditional loads (count >= 1)
+        pair[k] = pairs[item_at(t0, local_index<kFineItems>(wave, k, lane), count - 1)];
     // the order inside a window is free: a slot per item from one LDS atomic
 #pragma unroll
-    for (int k = 0; k < kItems; ++k)
-        slot[k] = local_index(wave, k, lane) < count ? atomicAdd(&cnt[(id[k] >> fshift) & fmask], 1u) : 0u;
+    for (int k = 0; k < kFineItems; ++k)
+        slot[k] = local_index<kFineItems>(wave, k, lane) < count
+                      ? atomicAdd(&cnt[((uint32_t)pair[k] >> fshift) & fmask], 1u)
+                      : 0u;
     __syncthreads();
     {
         uint32_t total;
         const uint32_t nw = tid <= (int)fmask ? cnt[tid] : 0u;  // the chunk's pairs of window digit tid
-        const uint32_t start = block_exclusive_scan<uint32_t>(nw, &total);
-        dstart[tid] = start;
-        const int64_t w = ((c >> qlog) << flog) | tid;
-        gbase[tid] = nw ? (uint32_t)(w << fshift) + atomicAdd(&wfill[w], nw) - start : 0u;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < kItems; ++k) {
-        if (local_index(wave, k, lane) < count) {
-            const uint32_t at = dstart[(id[k] >> fshift) & fmask] + slot[k];
-            if (at < (uint32_t)kTile) {
-                sid[at] = id[k];
-                spos[at] = pos[k];
-            }
+        const uint32_t start = block_exclusive_scan<uint32_t, kFineThreads>(nw, &total);
+        if (tid < kRadix) {
+            dstart[tid] = start;
+            const int64_t w = ((c >> qlog) << flog) | tid;
+            gbase[tid] = nw ? (uint32_t)(w << fshift) + atomicAdd(&wfill[w], nw) - start : 0u;
         }
     }
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < kItems; ++j) {
-        const int p = tid + j * kThreads;
+    for (int k = 0; k < kFineItems; ++k) {
+        if (local_index<kFineItems>(wave, k, lane) < count) {
+            const uint32_t at = dstart[((uint32_t)pair[k] >> fshift) & fmask] + slot[k];
+            if (at < (uint32_t)kTile) st[at] = pair[k];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kFineItems; ++j) {
+        const int p = tid + j * kFineThreads;
         if (p < count) {
-            const uint32_t who = sid[p];
-            const uint32_t dst = gbase[(who >> fshift) & fmask] + (uint32_t)p;
+            const uint64_t who = st[p];
+            const uint32_t dst = gbase[((uint32_t)who >> fshift) & fmask] + (uint32_t)p;
             if ((int64_t)dst < n) {
-                out_id[dst] = (uint16_t)(who & ((1u << fshift) - 1u));  // the id within its window
-                out_pos[dst] = spos[p];
+                out_id[dst] = (uint16_t)((uint32_t)who & ((1u << fshift) - 1u));  // the id within its window
+                out_pos[dst] = pair_pos(who);
             }
         }
     }
@@ -723,11 +762,12 @@ __global__ __launch_bounds__(kThreads) void k_fine_scatter(const uint32_t *in_id
 constexpr int kInvThreads = 1024;
 constexpr int kInvUnroll = 4;
 
-// ID: uint32_t ids (windows straight from the coarse buckets), or uint16_t
-// ids relative to the window's first id (written by the fine level).
-template <int kWinLog, typename ID>
-__global__ __launch_bounds__(kInvThreads) void k_invert_window(const ID *__restrict__ pair_id,
-                                                               const int32_t *__restrict__ pair_pos,
+// kFine: ids relative to the window's first id (2 bytes) and positions, as
+// the fine level writes them; else pairs, straight from the coarse buckets.
+template <int kWinLog, bool kFine>
+__global__ __launch_bounds__(kInvThreads) void k_invert_window(const uint64_t *__restrict__ pairs,
+                                                               const uint16_t *__restrict__ win_id,
+                                                               const int32_t *__restrict__ win_pos,
                                                                int64_t n, int wshift,
                                                                int32_t *__restrict__ order)
 {
@@ -743,9 +783,16 @@ __global__ __launch_bounds__(kInvThreads) void k_invert_window(const ID *__restr
         for (int u = 0; u < kInvUnroll; ++u) {  // unconditional loads (cnt >= 1)
             const int i = i0 + u * kInvThreads + (int)threadIdx.x;
             const int64_t at = base + (i < cnt ? i : cnt - 1);
-            const int64_t v = (int64_t)pair_id[at];
-            r[u] = pair_pos[at];
-            off[u] = i >= cnt ? -1 : (sizeof(ID) == 2 ? v : v - base);
+            int64_t v;
+            if constexpr (kFine) {
+                v = (int64_t)win_id[at];
+                r[u] = win_pos[at];
+            } else {
+                const uint64_t p = pairs[at];
+                v = (int64_t)(uint32_t)p - base;
+                r[u] = pair_pos(p);
+            }
+            off[u] = i >= cnt ? -1 : v;
         }
 #pragma unroll
         for (int u = 0; u < kInvUnroll; ++u)
@@ -1058,9 +1105,11 @@ OrderLayout order_layout(int64_t n)
     const int64_t clen = chunks * kRadix;
     OrderLayout L{};
     size_t off = 0;
+    // (the last pass's pairs lie over one pair of buffers, which follow each
+    // other)
     L.keys0 = off; off += align_up((size_t)n * sizeof(K), 256);
-    L.keys1 = off; off += align_up((size_t)n * sizeof(K), 256);
     L.ids0 = off; off += align_up((size_t)n * 4, 256);
+    L.keys1 = off; off += align_up((size_t)n * sizeof(K), 256);
     L.ids1 = off; off += align_up((size_t)n * 4, 256);
     L.counts = off; off += align_up((size_t)clen * 4, 256);
     L.partials = off; off += scan_partials_bytes(clen, 4);
@@ -1136,7 +1185,7 @@ int radix_mid_pass(int ks, int kd, const PassArgs &A)
 template <typename KS, bool kField>
 void last_pass(const void *src, const uint32_t *sids, int64_t n, int shift, const InvertPlan &P,
                uint32_t *counts, uint32_t *partials, uint32_t *bfill, uint32_t *flags, const int64_t *foff,
-               int nfields, uint32_t *aid, int32_t *apos, hipStream_t s)
+               int nfields, uint64_t *pairs, hipStream_t s)
 {
     constexpr int kW = pass_threads<KS>();
     const int64_t nt = (n + kW * kItems - 1) / (kW * kItems);
@@ -1144,7 +1193,7 @@ void last_pass(const void *src, const uint32_t *sids, int64_t n, int shift, cons
                        shift, counts, nt, flags, kField ? sids : nullptr, foff, nfields);
     exclusive_scan<uint32_t>(counts, nt * kRadix, partials, s);
     hipLaunchKernelGGL((k_scatter_last<KS, kW, kField>), dim3((unsigned)nt), dim3(kW), 0, s, (const KS *)src,
-                       sids, n, shift, counts, bfill, nt, foff, nfields, P.bshift, aid, apos);
+                       sids, n, shift, counts, bfill, nt, foff, nfields, P.bshift, pairs);
 }
 
 __global__ void k_zero_words(uint32_t *__restrict__ w, int64_t nw)
@@ -1242,40 +1291,35 @@ int run_order(const void *values, int64_t n, int passes, int32_t *order, char *w
         }
         // level 0 into the free buffers; level 1 back into the last pass's
         // source buffers once they are read
-        uint32_t *aid = (uint32_t *)keys[p & 1];
-        int32_t *apos = (int32_t *)ids[p & 1];
+        uint64_t *pairs = (uint64_t *)keys[p & 1];  // 8 n bytes: the keys, and the ids after them
         const int64_t nfill = fill_words(n, P);
         hipLaunchKernelGGL(k_zero_words, dim3((unsigned)((nfill + 255) / 256)), dim3(256), 0, s, bfill, nfill);
         if (field_last)
-            last_pass<uint32_t, true>(src, sids, n, 0, P, counts, partials, bfill, flags, foff, nfields, aid,
-                                      apos, s);
+            last_pass<uint32_t, true>(src, sids, n, 0, P, counts, partials, bfill, flags, foff, nfields, pairs,
+                                      s);
         else if (strip)
-            last_pass<uint8_t, false>(src, sids, n, 0, P, counts, partials, bfill, flags, foff, nfields, aid,
-                                      apos, s);
+            last_pass<uint8_t, false>(src, sids, n, 0, P, counts, partials, bfill, flags, foff, nfields, pairs,
+                                      s);
         else
             last_pass<uint64_t, false>(src, sids, n, shift, P, counts, partials, bfill, flags, foff, nfields,
-                                       aid, apos, s);
+                                       pairs, s);
         const int64_t nwin = (n + (1ll << P.wshift) - 1) >> P.wshift;
         if (P.wshift > kMaxWinLog + 1) return DMS_E_SIZE;
         if (P.fine) {
             uint16_t *fid = (uint16_t *)keys[(p - 1) & 1];
             int32_t *fpos = (int32_t *)ids[(p - 1) & 1];
-            const dim3 cgrid((unsigned)P.nchunks);
-            hipLaunchKernelGGL(k_fine_scatter, cgrid, dim3(kThreads), 0, s, aid, apos, n, P.fshift, P.flog,
-                               P.qlog, P.nchunks, wfill, fid, fpos);
+            hipLaunchKernelGGL(k_fine_scatter, dim3((unsigned)P.nchunks), dim3(kFineThreads), 0, s, pairs, n,
+                               P.fshift, P.flog, P.qlog, P.nchunks, wfill, fid, fpos);
             if (P.wshift <= kMaxWinLog)
-                hipLaunchKernelGGL((k_invert_window<kMaxWinLog, uint16_t>), dim3((unsigned)nwin),
-                                   dim3(kInvThreads), 0, s, fid, fpos, n, P.wshift, order);
+                hipLaunchKernelGGL((k_invert_window<kMaxWinLog, true>), dim3((unsigned)nwin), dim3(kInvThreads), 0, s,
+                                   pairs, fid, fpos, n, P.wshift, order);
             else
-                hipLaunchKernelGGL((k_invert_window<kMaxWinLog + 1, uint16_t>), dim3((unsigned)nwin),
-                                   dim3(kInvThreads), 0, s, fid, fpos, n, P.wshift, order);
+                hipLaunchKernelGGL((k_invert_window<kMaxWinLog + 1, true>), dim3((unsigned)nwin), dim3(kInvThreads),
+                                   0, s, pairs, fid, fpos, n, P.wshift, order);
         } else {
-            if (P.wshift <= kMaxWinLog)
-                hipLaunchKernelGGL((k_invert_window<kMaxWinLog, uint32_t>), dim3((unsigned)nwin),
-                                   dim3(kInvThreads), 0, s, aid, apos, n, P.wshift, order);
-            else
-                hipLaunchKernelGGL((k_invert_window<kMaxWinLog + 1, uint32_t>), dim3((unsigned)nwin),
-                                   dim3(kInvThreads), 0, s, aid, apos, n, P.wshift, order);
+            // (coarse buckets of at most 2^kMaxWinLog ids)
+            hipLaunchKernelGGL((k_invert_window<kMaxWinLog, false>), dim3((unsigned)nwin), dim3(kInvThreads), 0, s,
+                               pairs, (const uint16_t *)nullptr, (const int32_t *)nullptr, n, P.wshift, order);
         }
     }
     return launch_status();

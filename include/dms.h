@@ -128,10 +128,11 @@ int dms_order(const void *values, int dtype, int64_t n, int32_t *order, void *wo
  * injective int32 labelling with the same relative order (values must be
  * < 2^31 - 1).  An empty box is allowed and enqueues nothing.
  * workspace: dms_gradient_workspace_size(dims, lo, hi) bytes (about one
- * byte per box vertex) holding a queue through which vertices whose lower
- * star needs the full pairing loop are gathered and paired in dense waves;
- * or NULL (with workspace_bytes 0), in which case they are paired where
- * they are found -- the same records, slower on smooth fields.
+ * byte per box vertex) holding a queue of the vertices that no lower-star
+ * table covers, solved in full waves, and a list of the tiles that hold many
+ * of them (unused by boxes of at most 256 tiles); or NULL (with
+ * workspace_bytes 0), in which case every tile is taken a second time for
+ * them -- the same records, slower on smooth fields.
  * critical_mask: NULL, or ceil(nbox / 32) device uint32 (nbox = vertices of
  * the box) that receive one bit per record in box order, bit r % 32 of word
  * r / 32 set iff L(x) of record r holds a critical cell; every word is

@@ -2,11 +2,13 @@
 // (ensemble members or time steps) through order -> gradient -> critical
 // simplices with one graph launch.
 //
-// All fields are concatenated.  The order is one radix sort on a composite
-// key (field index above the float32 value key), so each field's ranks are
-// its global positions minus the field's offset.  The gradient is one
-// launch over the (field, tile) list, a block per tile; the extraction one
-// pass over the records the gradient flagged in its critical mask.  The first run records these launches into a hipGraph on a
+// All fields are concatenated.  The order is one radix sort by (field, value):
+// the value passes and then one by the field of each id, or a composite key
+// (the field index above the float32 value key); each field's ranks are its
+// global positions minus the field's offset.  The gradient is one launch over
+// the (field, tile) list, a block per tile, with the dense and queue kernels
+// behind it; the extraction one pass over the records the gradient flagged in
+// its critical mask.  The first run records these launches into a hipGraph on a
 // private capture stream; later runs with the same arguments replay it on the
 // caller's stream.  An autotuner picks the gradient tile shape per batch
 // (timed on the first run, remembered in an optional cache file).

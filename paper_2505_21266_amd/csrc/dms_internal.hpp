@@ -5,7 +5,7 @@
 
 namespace dms {
 
-// Largest number of fields in one batch (their tables live in LDS).
+// Largest number of fields in one batch.
 constexpr int kMaxBatchFields = 1024;
 
 // One field of a batch: dims (x, y, z) and its offset in the concatenated

@@ -297,10 +297,12 @@ struct NoKey {};
 // The lanes holding the same digit are found either by eight ballots
 // (kLds false) or through LDS (kLds true): each lane ORs its lane bit into
 // the wave's mask slot of its digit (mk, zero between uses), reads the slot
-// back and clears it -- three LDS operations in place of some forty vector
-// instructions, which pays where the vector units are the busier resource
-// (measured per kernel: the radix scatters and the id buckets use LDS, the
-// last pass's digit and the fine partition the ballots).  A wave whose lanes share one digit (the high bytes of a smooth
+// back and clears it -- three LDS operations in place of some thirty vector
+// instructions.  Random digits go through LDS: the scatters of the first three
+// passes over 1.08e9 keys take 3.51, 3.32 and 3.20 ms so, 3.58, 3.54 and 3.30
+// with ballots, 3.54, 3.50 and 3.31 with every other item by ballots.  The
+// last pass's digit takes few values, which meet on few masks: it goes by
+// ballots.  A wave whose lanes share one digit (the high bytes of a smooth
 // field) skips either.
 template <bool kLds, typename CT>
 __device__ __forceinline__ uint32_t wave_rank(uint32_t d, bool valid, CT *wh, uint64_t *mk)

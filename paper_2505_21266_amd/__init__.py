@@ -178,23 +178,6 @@ def star_tables():
     return dict(nb=nb, tri=tri, tet=tet, edge_tris=et, tri_tets=tt)
 
 
-class Workspace:
-    """A growable device byte buffer reused across calls."""
-
-    def __init__(self):
-        self.buf = None
-
-    def get(self, nbytes, device):
-        import torch
-        if self.buf is None or self.buf.numel() < nbytes or self.buf.device != device:
-            self.buf = torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
-        return self.buf
-
-
-_ws_order = Workspace()
-_ws_crit = Workspace()
-
-
 def new_flags(device):
     import torch
     return torch.zeros(1, dtype=torch.int32, device=device)
@@ -254,8 +237,7 @@ def order(values, out=None, flags=None, check=True):
     own_flags = flags is None
     if own_flags:
         flags = new_flags(values.device)
-    nbytes = L.dms_order_workspace_size(n, dt)
-    ws = _ws_order.get(nbytes, values.device)
+    ws = torch.empty(max(int(L.dms_order_workspace_size(n, dt)), 256), dtype=torch.uint8, device=values.device)
     _check(L.dms_order(_ptr(values), dt, n, _ptr(out), _ptr(ws), ws.numel(), _ptr(flags),
                        _stream(values)), "dms_order")
     if check and own_flags:
@@ -383,7 +365,8 @@ def critical_simplices(rec, dims, lo=None, hi=None, cap=None, flags=None, counts
     cap: per-dimension capacities; None sizes the lists exactly (one extra
     counting call and a sync).  mask: the critical mask the gradient call
     wrote with rec (only flagged records are read), or None.  Returns
-    (lists, counts tensor).
+    (lists, counts tensor), written in the order of the current stream: lists
+    sized by the counting call are still being filled on return.
     """
     _require_gpu(rec, "rec")
     own_flags, sized = flags is None, cap is not None
@@ -409,7 +392,7 @@ def _list_cells(rec, dims, lo, hi, cap, mask, counts=None, flags=None):
     h, hp = _arr3(hi)
     L = lib()
     mp = _mask_ptr(mask, max(0, hi[0] - lo[0]) * max(0, hi[1] - lo[1]) * max(0, hi[2] - lo[2]))
-    ws = _ws_crit.get(L.dms_critical_workspace_size(dp, lp, hp), dev)
+    ws = torch.empty(max(int(L.dms_critical_workspace_size(dp, lp, hp)), 256), dtype=torch.uint8, device=dev)
     if counts is None:
         counts = torch.zeros(4, dtype=torch.int64, device=dev)
     if flags is None:
@@ -646,7 +629,8 @@ def d2_pairs(rec, order_t, dims, crit2, crit3):
 def gradient_pipeline(values, lo=None, hi=None, cap=None):
     """order -> discrete gradient -> critical simplices for one field (the
     gradient marks the records holding critical cells; the extraction reads
-    only those)."""
+    only those).  Without cap the lists are still being filled on return, in
+    the order of the current stream."""
     flags = new_flags(values.device)
     o = order(values, flags=flags, check=False)
     dims = dims_of(values)

@@ -10,6 +10,7 @@ are (nx, ny, nz).  Boxes are half-open (x, y, z) bounds [lo, hi).
 """
 import ctypes
 import os
+import struct
 
 import numpy as np
 
@@ -127,13 +128,19 @@ def init(device=None):
     _ready.add(idx)
 
 
-_Int64x3, _Int64x4 = ctypes.c_int64 * 3, ctypes.c_int64 * 4
+def _int64s(v, n):
+    """n host int64 as a ctypes array, from any form that numpy reads as n
+    integers (n plain integers without it: half the time)."""
+    try:
+        raw = struct.pack("%dq" % n, *v)
+    except (struct.error, TypeError):
+        raw = np.asarray(v, dtype=np.int64).reshape(n).tobytes()
+    return (ctypes.c_int64 * n).from_buffer_copy(raw)
 
 
 def _arr3(v):
-    """Three host int64 as a ctypes array (twice: to keep, and to pass as the pointer)."""
-    x, y, z = v
-    a = _Int64x3(int(x), int(y), int(z))
+    """Three host int64 (twice: the array to keep, and to pass as the pointer)."""
+    a = _int64s(v, 3)
     return a, a
 
 
@@ -397,7 +404,7 @@ def _list_cells(rec, dims, lo, hi, cap, mask, counts=None, flags=None):
         counts = torch.zeros(4, dtype=torch.int64, device=dev)
     if flags is None:
         flags = new_flags(dev)
-    capa = _Int64x4(*(int(c) for c in np.asarray(cap).reshape(4)))
+    capa = _int64s(cap, 4)
     lists = [torch.empty(max(c, 0), dtype=torch.int64, device=dev) for c in capa]
     _check(L.dms_critical_simplices(_ptr(rec), mp, dp, lp, hp, _ptr(lists[0]), _ptr(lists[1]),
                                     _ptr(lists[2]), _ptr(lists[3]), capa, _ptr(counts), _ptr(ws),
@@ -431,7 +438,7 @@ def critical_simplices_noalloc(rec, dims, cap, lo=None, hi=None, lists=None, cou
     d, dp = _arr3(dims)
     l, lp = _arr3(lo)
     h, hp = _arr3(hi)
-    capa = _Int64x4(*(int(c) for c in np.asarray(cap).reshape(4)))
+    capa = _int64s(cap, 4)
     if lists is None:
         lists = [torch.empty(int(max(c, 0)), dtype=torch.int64, device=dev) for c in capa]
     if counts is None:

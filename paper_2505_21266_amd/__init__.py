@@ -638,6 +638,7 @@ def gradient_pipeline(values, lo=None, hi=None, cap=None):
     gradient marks the records holding critical cells; the extraction reads
     only those).  Without cap the lists are still being filled on return, in
     the order of the current stream."""
+    _require_gpu(values, "values")
     flags = new_flags(values.device)
     o = order(values, flags=flags, check=False)
     dims = dims_of(values)

@@ -51,3 +51,10 @@ def test_capacities(cap):
 def test_capacities_beyond_64_bits(cap):
     with pytest.raises(OverflowError):
         dms._int64s(cap, 4)
+
+
+@pytest.mark.parametrize("values", [[0.5, 1.0], 3.0, np.zeros((2, 2, 2), np.float32), None],
+                         ids=["list", "number", "array", "none"])
+def test_pipeline_refuses_host_values(values):
+    with pytest.raises(TypeError, match="GPU tensor"):
+        dms.gradient_pipeline(values)

@@ -886,7 +886,7 @@ constexpr int kGroupWords = kGroupRecs / 32;
 static_assert(kGroups * sizeof(uint64_t) <= kCand * sizeof(uint16_t), "group counts in the candidates' space");
 
 // Counts a tile: groups[tile * kGroups + g] = packed counts of the tile's
-// groups before g.
+// groups up to g.
 __global__ __launch_bounds__(kThreads) void k_short_count(const uint4 *__restrict__ rec,
                                                           const uint32_t *__restrict__ mask, int64_t nbox,
                                                           uint64_t *__restrict__ tile_counts, int64_t ntiles,
@@ -918,15 +918,14 @@ __global__ __launch_bounds__(kThreads) void k_short_count(const uint4 *__restric
         if (lane == 0) gsum[wave * (kGroups / kWavesPerBlock) + g] = sum;
     }
     __syncthreads();
-    if (tid <= kGroups) {
-        uint64_t before = 0;
+    if (tid < kGroups) {
+        uint64_t upto = 0;
 #pragma unroll
-        for (int g = 0; g < kGroups; ++g) before += g < tid ? gsum[g] : 0;
-        if (tid < kGroups) {
-            groups[tile * kGroups + tid] = before;
-        } else {
+        for (int g = 0; g < kGroups; ++g) upto += g <= tid ? gsum[g] : 0;
+        groups[tile * kGroups + tid] = upto;
+        if (tid == kGroups - 1) {
 #pragma unroll
-            for (int d = 0; d < 4; ++d) tile_counts[(int64_t)d * ntiles + tile] = lane16(before, d);
+            for (int d = 0; d < 4; ++d) tile_counts[(int64_t)d * ntiles + tile] = lane16(upto, d);
         }
     }
     if (tile == 0 && tid == kWave) tile_counts[4 * ntiles] = 0;
@@ -973,7 +972,9 @@ __global__ __launch_bounds__(kShortScan) void k_short_scan(uint64_t *__restrict_
     finish_counts(tc, ntiles, counts, cap0, cap1, cap2, cap3, flags);
 }
 
-// Fills the cells of one group a wave, its (flagged) records kWave at a time.
+// Fills the cells of one group a wave, its (flagged) records kWave at a time.  A
+// group that the count found empty is not read: without a mask that is all but
+// a few of a smooth field's.
 // foff: offsets of a batch's fields (codes carry the field-local vertex), or
 // null for the box of a single field.
 __global__ __launch_bounds__(kThreads) void k_short_fill(
@@ -991,6 +992,8 @@ __global__ __launch_bounds__(kThreads) void k_short_fill(
     const int64_t r0 = group * kGroupRecs;
     if (r0 >= nbox) return;
     const int64_t tile = group / kGroups;
+    const uint64_t before = group % kGroups ? groups[group - 1] : 0u;
+    if (groups[group] == before) return;  // uniform
     // the group's mask words in the first lanes (all records flagged without a mask)
     uint32_t word = 0;
     if (lane < kGroupWords) {
@@ -999,7 +1002,6 @@ __global__ __launch_bounds__(kThreads) void k_short_fill(
             word = mask ? mask[group * kGroupWords + lane] : left >= 32 ? ~0u : (1u << (uint32_t)left) - 1u;
     }
     if (!__ballot(word != 0u)) return;
-    const uint64_t before = groups[group];
     uint64_t at[4];
 #pragma unroll
     for (int d = 0; d < 4; ++d)

@@ -679,9 +679,11 @@ __device__ __forceinline__ int64_t entry_record(const uint4 &e)
 
 // The queue and the list of dense tiles, in the caller's workspace: a queue
 // counter and a list counter, then the entries, then the tile numbers.  A
-// counter may pass its capacity: entries beyond are not written.  A tile whose
-// vertices do not all fit the queue is listed; when the list is full too, or
-// there is no workspace (all null), the dense kernel takes every tile.
+// counter may pass its capacity: entries beyond are not written (a launch has
+// fewer than 2^24 tiles, its work items being a 32-bit number, and each adds less
+// than kThreads to the queue's: it stays below 2^32).  A tile whose vertices do
+// not all fit the queue solves the rest or is listed; when the list is full too,
+// or there is no workspace (all null), the dense kernel takes every tile.
 struct Handoff {
     uint32_t *counts;  // [0] queue, [1] list
     uint4 *queue;
@@ -855,6 +857,18 @@ __device__ __forceinline__ bool skip_tables(bool in, bool gen)
 // addresses.  With a pointer, a branch and a loop per family, 1026^3 / 512^3 of
 // ranks and 512^3 of float values took 11.6 / 5.0 / 4.7 ms; now
 // 10.2 / 3.5 / 3.0 ms with the general vertices' kernels.
+//
+// The queue has room for one vertex in 16.  Fields with short sides have more
+// general vertices (all of the boundary), and fill it.  The rest of a tile is
+// then solved in its block while its neighbours are sorted and at hand; listed
+// with the dense tiles, it is staged and searched again: 20 x 300 x 300 smooth
+// ranks took 171 us so, now 98, a batch of 1000 smooth fields with sides 20..40
+// 3.26 ms, now 2.40.  A launch of up to kListTiles tiles lists them: the dense
+// kernel runs beside an idle chip there, and spreads a tile over four blocks (12
+// fields, 758 tiles: 174 us of kernels, 180 when solved in the tile; 1200 tiles
+// of 40 x 40 x 400: 65 and 61 us).
+constexpr uint32_t kListTiles = 1024;
+
 struct TileShared {
     uint32_t qbase, nlist;
     uint16_t list[kTileVerts];  // general vertices of the tile (tile positions)
@@ -955,10 +969,26 @@ __device__ __forceinline__ void gradient_tile(const void *__restrict__ field, co
         __syncthreads();
         // as many as fit are queued, so that every slot the queue kernel
         // reads, [0, min(count, qcap)), has been written by this launch
+        const int64_t ridx = rbase + tx + w0 * ty;
         const uint32_t qb = sh.qbase;
         const uint32_t nq = qb >= Q.qcap ? 0u : min(total, Q.qcap - qb);  // uniform
-        if ((uint32_t)tid < nq) Q.queue[qb + tid] = queue_entry(nb_at, rbase + tx + w0 * ty, low);
-        dense = nq < total;  // listed too: the dense kernel solves all of the tile's general vertices
+        if ((uint32_t)tid < nq) Q.queue[qb + tid] = queue_entry(nb_at, ridx, low);
+        if (nq == total) return;
+        if (gridDim.x > kListTiles) {
+            // solved here, with the tables in place of the halo
+            static_assert(sizeof(StarTables) <= sizeof(typename Keys::H) * S::kHalo, "tables in the halo's space");
+            StarTables &T = *(StarTables *)tile;
+            load_tables(T);
+            __syncthreads();
+            if (mine && (uint32_t)tid >= nq) {
+                uint4 r;
+                const bool crit = solve_star(nb_at, low, T, r);
+                rec[ridx] = r;
+                if (mark && crit) mark_critical(mark, ridx);
+            }
+            return;
+        }
+        dense = true;  // listed too: the dense kernel solves all of the tile's general vertices
     }
     if (dense && tid == 0) {
         const uint32_t at = atomicAdd(&Q.counts[1], 1u);
@@ -1007,7 +1037,7 @@ __global__ __launch_bounds__(kThreads, 8) void k_gradient(const void *__restrict
                                                           uint32_t *flags, uint32_t *__restrict__ mark)
 {
     __shared__ TileShared sh;
-    __shared__ typename Keys::H tile[Tile<GX, GY>::kHalo];
+    __shared__ __align__(16) typename Keys::H tile[Tile<GX, GY>::kHalo];
     const uint32_t t = chunked_tile(blockIdx.x, gridDim.x);
     const TileAt T = tile_at(t, (uint32_t)B.w2, bx_count);
     const int64_t bx = T.x, by = T.y, bz = T.z;
@@ -1046,7 +1076,7 @@ __global__ __launch_bounds__(kThreads, 8) void k_gradient_batch(const int32_t *_
                                                                 uint32_t *__restrict__ mark)
 {
     __shared__ TileShared sh;
-    __shared__ int32_t tile[Tile<GX, GY>::kHalo];
+    __shared__ __align__(16) int32_t tile[Tile<GX, GY>::kHalo];
     int64_t bx, by, bz;
     const uint32_t t = chunked_tile(blockIdx.x, gridDim.x);
     const Box B = batch_box<GX, GY>(L, t, bx, by, bz);

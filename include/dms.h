@@ -131,8 +131,9 @@ int dms_order(const void *values, int dtype, int64_t n, int32_t *order, void *wo
  * byte per box vertex) holding a queue of the vertices that no lower-star
  * table covers, solved in full waves, and a list of the tiles that hold many
  * of them (unused by boxes of at most 256 tiles); or NULL (with
- * workspace_bytes 0), in which case every tile is taken a second time for
- * them -- the same records, slower on smooth fields.
+ * workspace_bytes 0), in which case a tile of 64 x 16 vertices solves a few of
+ * them itself and one with many is taken a second time (every tile is, in
+ * small boxes) -- the same records.
  * critical_mask: NULL, or ceil(nbox / 32) device uint32 (nbox = vertices of
  * the box) that receive one bit per record in box order, bit r % 32 of word
  * r / 32 set iff L(x) of record r holds a critical cell; every word is

@@ -299,8 +299,9 @@ def _mask_ptr(mask, nbox):
 def discrete_gradient(order_t, lo=None, hi=None, out=None, queue=True, workspace=None, mask=None):
     """Lower-star records (dms_discrete_gradient): int32 tensor (nbox, 4)
     holding the 128-bit records (reinterpret as uint32).  queue=False passes
-    no workspace (general vertices are then paired inside their tiles);
-    workspace (from gradient_workspace) avoids an allocation per call;
+    no workspace (a tile then solves its few general vertices itself, or is
+    taken a second time for its many); workspace (from gradient_workspace)
+    avoids an allocation per call;
     mask (from critical_mask) receives the bits of the records that hold a
     critical cell, for critical_simplices."""
     import torch

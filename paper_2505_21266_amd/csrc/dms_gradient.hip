@@ -682,8 +682,10 @@ __device__ __forceinline__ int64_t entry_record(const uint4 &e)
 // counter may pass its capacity: entries beyond are not written (a launch has
 // fewer than 2^24 tiles, its work items being a 32-bit number, and each adds less
 // than kThreads to the queue's: it stays below 2^32).  A tile whose vertices do
-// not all fit the queue solves the rest or is listed; when the list is full too,
-// or there is no workspace (all null), the dense kernel takes every tile.
+// not all fit the queue solves the rest or is listed; when the list is full too
+// the dense kernel takes every tile.  Without a workspace (all null) it does so
+// in small launches; in others a tile with few vertices solves them itself, and
+// a dense one marks one of its records.
 struct Handoff {
     uint32_t *counts;  // [0] queue, [1] list
     uint4 *queue;
@@ -713,6 +715,10 @@ __device__ __forceinline__ void scan_bins(uint32_t *bins)
         if (tid < kSizeBins) bins[tid] = inc - v;
     }
 }
+
+// First word of a dense tile's first record where there is no list: no record
+// has it (edge fields end at 8).
+constexpr uint32_t kDenseTile = 0xffffffffu;
 
 // Marks record r (box index) as holding a critical cell: bit r of the mask.
 __device__ __forceinline__ void mark_critical(uint32_t *mark, int64_t r)
@@ -869,6 +875,13 @@ __device__ __forceinline__ bool skip_tables(bool in, bool gen)
 // of 40 x 40 x 400: 65 and 61 us).
 constexpr uint32_t kListTiles = 1024;
 
+// Without a workspace, a launch of up to this many tiles leaves all general
+// vertices to the dense kernel, a larger one marks its dense tiles.  Smooth and
+// noise ranks, smooth values in double precision, us: 2048 tiles 58 / 97 / 116
+// and, marked, 56 / 104 / 122; 3072 tiles 77 / 148 / 170 and 67 / 153 / 137; 8192
+// tiles 194 / 370 / 410 and 116 / 374 / 263.
+constexpr uint32_t kMarkTiles = 2048;
+
 struct TileShared {
     uint32_t qbase, nlist;
     uint16_t list[kTileVerts];  // general vertices of the tile (tile positions)
@@ -949,11 +962,18 @@ __device__ __forceinline__ void gradient_tile(const void *__restrict__ field, co
     if (total == 0) return;
 
     const Handoff Q = H;
-    if (!Q.counts) return;  // the dense kernel takes every tile
     bool dense = total >= (uint32_t)kThreads;
+    if (!Q.counts) {
+        if (gridDim.x <= kMarkTiles) return;
+        if (dense) {
+            // (by the thread that stored the table entry there, if it has one)
+            if (tid == 0) store_record(rec + rbase, kDenseTile, kDenseTile, kDenseTile, kDenseTile);
+            return;
+        }
+    }
     if (!dense) {
         // reserve queue slots; the sorting below overlaps the atomic
-        if (tid == 0) sh.qbase = atomicAdd(&Q.counts[0], total);
+        if (tid == 0) sh.qbase = Q.counts ? atomicAdd(&Q.counts[0], total) : 0u;
         const bool mine = (uint32_t)tid < total;
         const int v = mine ? sh.list[tid] : 0;
         const int tx = v % GX, ty = v / GX;
@@ -974,7 +994,7 @@ __device__ __forceinline__ void gradient_tile(const void *__restrict__ field, co
         const uint32_t nq = qb >= Q.qcap ? 0u : min(total, Q.qcap - qb);  // uniform
         if ((uint32_t)tid < nq) Q.queue[qb + tid] = queue_entry(nb_at, ridx, low);
         if (nq == total) return;
-        if (gridDim.x > kListTiles) {
+        if (gridDim.x > kListTiles || !Q.counts) {
             // solved here, with the tables in place of the halo
             static_assert(sizeof(StarTables) <= sizeof(typename Keys::H) * S::kHalo, "tables in the halo's space");
             StarTables &T = *(StarTables *)tile;
@@ -1087,7 +1107,8 @@ __global__ __launch_bounds__(kThreads, 8) void k_gradient_batch(const int32_t *_
 // All vertices of one tile that gradient_tile left (whole: all of its
 // vertices), solved in rounds of kThreads, dealt by the number of lower
 // neighbours.  part of parts (1 or 4): the quarter of the tile's positions
-// this block takes.
+// this block takes.  first: position 0 is solved in any case (its record holds
+// the tile's mark).
 struct DenseShared {
     StarTables T;
     uint32_t bins[kSizeBins];
@@ -1097,7 +1118,7 @@ struct DenseShared {
 
 template <typename Keys, int GX, int GY>
 __device__ __forceinline__ void dense_tile(const void *__restrict__ field, const Box &B, int64_t bx, int64_t by,
-                                           int64_t bz, int part, int parts, bool whole,
+                                           int64_t bz, int part, int parts, bool whole, bool first,
                                            uint4 *__restrict__ rec, uint32_t *flags, uint32_t *__restrict__ mark,
                                            DenseShared &sh, typename Keys::H *tile)
 {
@@ -1123,7 +1144,7 @@ __device__ __forceinline__ void dense_tile(const void *__restrict__ field, const
         const uint32_t low = lower_mask(o, ox);
         const bool gen = general_vertex(low);
         if (k == 0) skip = skip_tables(in, gen);
-        if (mine && in && (gen || whole || skip)) {
+        if (mine && in && (gen || whole || skip || (first && v == 0))) {
             const uint32_t m = (uint32_t)__popc(low);
             sizes |= (128u | m) << (8 * k);
             atomicAdd(&sh.bins[m], 1u);
@@ -1205,8 +1226,49 @@ __global__ __launch_bounds__(kThreads, 6) void k_gradient_dense(const void *__re
     dense_walk(H, ntiles, [&](uint32_t t, int part, int parts) {
         const TileAt T = tile_at(t, (uint32_t)B.w2, bx_count);
         const int64_t bx = T.x, by = T.y, bz = T.z;
-        dense_tile<Keys, GX, GY>(field, B, bx, by, bz, part, parts, whole, rec, flags, mark, sh, tile);
+        dense_tile<Keys, GX, GY>(field, B, bx, by, bz, part, parts, whole, false, rec, flags, mark, sh, tile);
     });
+}
+
+// The same without a workspace: the tiles that are marked.  A block asks for
+// kThreads of its tiles at once.  (With every tile staged and searched again the
+// gradient of a smooth 256^3 field took 367 us, of a 512^3 one 2.34 ms; now 166 us
+// and 1.05 ms.)
+// Its tiles are kMarkedBlocks apart, a prime, or a block could get a column's
+// bottom or top tile (all dense) every time: a smooth 256^3 field took 323 us with
+// kDenseBlocks.
+constexpr uint32_t kMarkedBlocks = 1531;
+static_assert(kMarkedBlocks <= kMarkTiles, "fewer blocks than tiles");
+
+template <typename Keys, int GX, int GY>
+__global__ __launch_bounds__(kThreads, 6) void k_gradient_marked(const void *__restrict__ field, Box B,
+                                                                 uint32_t bx_count, uint32_t ntiles,
+                                                                 uint4 *__restrict__ rec,
+                                                                 uint32_t *__restrict__ mark)
+{
+    __shared__ DenseShared sh;
+    __shared__ uint64_t found[kThreads / kWave];
+    __shared__ typename Keys::H tile[Tile<GX, GY>::kHalo];
+    load_tables(sh.T);
+    for (uint64_t t0 = blockIdx.x; t0 < ntiles; t0 += (uint64_t)gridDim.x * kThreads) {
+        const uint64_t mine = t0 + (uint64_t)gridDim.x * threadIdx.x;
+        bool marked = false;
+        if (mine < ntiles) {
+            const TileAt T = tile_at((uint32_t)mine, (uint32_t)B.w2, bx_count);
+            marked = rec[(int64_t)T.x * GX + B.w0 * ((int64_t)T.y * GY + B.w1 * T.z)].x == kDenseTile;
+        }
+        const uint64_t bits = __ballot(marked);
+        __syncthreads();
+        if (lane_id() == 0) found[threadIdx.x / kWave] = bits;
+        __syncthreads();
+        for (int w = 0; w < kThreads / kWave; ++w)
+            for (uint64_t left = found[w]; left; left &= left - 1u) {
+                const uint64_t t = t0 + (uint64_t)gridDim.x * (uint32_t)(kWave * w + __builtin_ctzll(left));
+                const TileAt T = tile_at((uint32_t)t, (uint32_t)B.w2, bx_count);
+                const int64_t bx = T.x, by = T.y, bz = T.z;
+                dense_tile<Keys, GX, GY>(field, B, bx, by, bz, 0, 1, false, true, rec, nullptr, mark, sh, tile);
+            }
+    }
 }
 
 template <int GX, int GY>
@@ -1221,8 +1283,8 @@ __global__ __launch_bounds__(kThreads, 6) void k_gradient_dense_batch(const int3
     dense_walk(H, ntiles, [&](uint32_t t, int part, int parts) {
         int64_t bx, by, bz;
         const Box B = batch_box<GX, GY>(L, t, bx, by, bz);
-        dense_tile<RankKeys, GX, GY>(order + B.rec_off, B, bx, by, bz, part, parts, whole, rec, nullptr, mark, sh,
-                                     tile);
+        dense_tile<RankKeys, GX, GY>(order + B.rec_off, B, bx, by, bz, part, parts, whole, false, rec, nullptr, mark,
+                                     sh, tile);
     });
 }
 
@@ -1491,8 +1553,12 @@ static int launch_gradient_keys(const void *field, const int64_t *dims, const in
     if (!whole)
         hipLaunchKernelGGL((k_gradient<Keys, kGX, kGY>), dim3((unsigned)blocks), dim3(kThreads), 0, s, field, B, (uint32_t)bxc,
                            (uint4 *)rec, device_tables(), H, flags, mark);
-    hipLaunchKernelGGL((k_gradient_dense<Keys, kGX, kGY>), dim3(dense_blocks(blocks)), dim3(kThreads), 0, s, field,
-                       B, (uint32_t)bxc, (uint32_t)blocks, whole, (uint4 *)rec, H, whole ? flags : nullptr, mark);
+    if (whole || H.counts || blocks <= (int64_t)kMarkTiles)
+        hipLaunchKernelGGL((k_gradient_dense<Keys, kGX, kGY>), dim3(dense_blocks(blocks)), dim3(kThreads), 0, s, field,
+                           B, (uint32_t)bxc, (uint32_t)blocks, whole, (uint4 *)rec, H, whole ? flags : nullptr, mark);
+    else
+        hipLaunchKernelGGL((k_gradient_marked<Keys, kGX, kGY>), dim3(kMarkedBlocks), dim3(kThreads), 0, s, field, B,
+                           (uint32_t)bxc, (uint32_t)blocks, (uint4 *)rec, mark);
     queue_finish(H, rec, mark, s);
     return launch_status();
 }

@@ -27,7 +27,7 @@ int init_tables(hipStream_t s);
 // scratch array (once per device).
 int init_critical_scratch();
 // ws: gradient_workspace_size(owned vertices) bytes for the queue of
-// general vertices and the list of dense tiles, or null (every tile's general
+// general vertices and the list of dense tiles, or null (the general
 // vertices are then solved tile by tile).
 size_t gradient_workspace_size(int64_t owned);
 // mark (may be null): one bit per concatenated record, set for the records

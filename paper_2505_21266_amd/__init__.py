@@ -566,7 +566,7 @@ def critical_sort(codes, dim, order_t, dims, out=None, flags=None, check=True):
 
 def d0_pairs(rec, order_t, dims, crit0, crit1):
     """D0 pairing: the extremum graph on the GPU (dms_d0_triplets: descents by
-    pointer doubling, triplets sorted by edge), Algorithm 1 on the host
+    pointer jumping, triplets sorted by edge), Algorithm 1 on the host
     (dms_d0_pairs_sorted_host).  rec/order_t/crit0/crit1 are device tensors
     of the whole grid.  Returns numpy (pair_edge codes, pair_min vertices)."""
     import torch
@@ -658,7 +658,7 @@ def gradient_pipeline(values, lo=None, hi=None, cap=None):
         lists, counts, flags = _list_cells(rec, dims, lo, hi, cap, mask, flags=flags)
         check_flags(flags)
         return o, rec, lists, counts
-    # one wait, for the counts that size the lists; a NaN is found there too
+    # the one wait is for the counts that size the lists; a NaN is found there too
     cap, counts, f = _count_cells(rec, dims, lo, hi, mask, flags=flags)
     _raise_flags(f)
     lists, counts, _ = _list_cells(rec, dims, lo, hi, cap, mask, counts)

@@ -861,8 +861,8 @@ __device__ __forceinline__ bool skip_tables(bool in, bool gen)
 // one 32-bit entry number (no branch or pointer per family), masks and digits
 // are built from borrow and carry bits, and a row's loads have scalar
 // addresses.  With a pointer, a branch and a loop per family, 1026^3 / 512^3 of
-// ranks and 512^3 of float values took 11.6 / 5.0 / 4.7 ms; now
-// 10.2 / 3.5 / 3.0 ms with the general vertices' kernels.
+// ranks took 11.6 / 5.0 ms with the general vertices' kernels; so, with the
+// records stored past the L2 and the tiles in chunks, 9.9 / 3.5 ms.
 //
 // The queue has room for one vertex in 16.  Fields with short sides have more
 // general vertices (all of the boundary), and fill it.  The rest of a tile is

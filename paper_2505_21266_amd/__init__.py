@@ -11,6 +11,7 @@ are (nx, ny, nz).  Boxes are half-open (x, y, z) bounds [lo, hi).
 import ctypes
 import os
 import struct
+import threading
 
 import numpy as np
 
@@ -185,6 +186,33 @@ def star_tables():
     return dict(nb=nb, tri=tri, tet=tet, edge_tris=et, tri_tets=tt)
 
 
+class Workspace:
+    """A growable device byte buffer, kept for the next call of the same thread
+    on the same stream.  A call of another thread or stream takes a new one and
+    keeps that instead; the old one goes back to the stream that it was used on.
+    (A new one for each call made a 1026^3 step 1.8% slower in processes that
+    had run other work before: 32.4 ms against 31.8.)  A call under capture
+    takes one of the graph's own memory."""
+
+    def __init__(self):
+        self.kept = (None, None)  # whose, buffer: replaced as one
+
+    def get(self, nbytes, device):
+        import torch
+        owner, buf = self.kept
+        mine = (threading.get_ident(), device, torch.cuda.current_stream(device).cuda_stream)
+        capturing = torch.cuda.is_current_stream_capturing()
+        if capturing or owner != mine or buf.numel() < nbytes:
+            buf = torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
+            if not capturing:
+                self.kept = (mine, buf)
+        return buf
+
+
+_ws_order = Workspace()
+_ws_crit = Workspace()
+
+
 def new_flags(device):
     import torch
     return torch.zeros(1, dtype=torch.int32, device=device)
@@ -252,7 +280,7 @@ def order(values, out=None, flags=None, check=True):
     own_flags = flags is None
     if own_flags:
         flags = new_flags(values.device)
-    ws = torch.empty(max(int(L.dms_order_workspace_size(n, dt)), 256), dtype=torch.uint8, device=values.device)
+    ws = _ws_order.get(L.dms_order_workspace_size(n, dt), values.device)
     _check(L.dms_order(_ptr(values), dt, n, _ptr(out), _ptr(ws), ws.numel(), _ptr(flags),
                        _stream(values)), "dms_order")
     if check and own_flags:
@@ -408,7 +436,7 @@ def _list_cells(rec, dims, lo, hi, cap, mask, counts=None, flags=None):
     h, hp = _arr3(hi)
     L = lib()
     mp = _mask_ptr(mask, max(0, hi[0] - lo[0]) * max(0, hi[1] - lo[1]) * max(0, hi[2] - lo[2]))
-    ws = torch.empty(max(int(L.dms_critical_workspace_size(dp, lp, hp)), 256), dtype=torch.uint8, device=dev)
+    ws = _ws_crit.get(L.dms_critical_workspace_size(dp, lp, hp), dev)
     if counts is None:
         counts = torch.zeros(4, dtype=torch.int64, device=dev)
     if flags is None:

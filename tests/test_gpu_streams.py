@@ -1,7 +1,9 @@
 """Default calls on two streams of one thread, with no wait of the caller's
-between them: each call's scratch is its own, so the lists of both fields equal
-the CPU oracle's.  The second field of a pair is the larger one, so the scratch
+between them, and of two threads on one stream: no two calls in flight share
+their scratch, so the lists of both fields equal the CPU oracle's.  The second field of a pair is the larger one, so the scratch
 of the call under way could neither be shared nor outgrown."""
+import threading
+
 import numpy as np
 import pytest
 
@@ -67,3 +69,38 @@ def test_two_streams_order():
     torch.cuda.synchronize()
     for i, o in enumerate(got):
         assert (o.cpu().numpy() == want[i % 2]).all(), i
+
+
+@pytest.mark.parametrize("own_streams", [False, True])
+def test_two_threads(own_streams):
+    dims = [(24, 20, 16), (64, 50, 41)]
+    cases = [_case(d, 3 + i) for i, d in enumerate(dims)]
+    torch.cuda.synchronize()
+    print("two threads", own_streams, flush=True)
+    got, errors = [[], []], []
+    start = threading.Barrier(2)
+
+    def work(i):
+        try:
+            start.wait(30)
+            with torch.cuda.stream(torch.cuda.Stream() if own_streams else None):
+                for _ in range(20):
+                    o, _, lists, _ = dms.gradient_pipeline(cases[i][0])
+                    got[i].append((o, lists))
+                    got[i].append((o, dms.critical_simplices(cases[i][2], dims[i])[0]))
+        except Exception as e:  # raised in the main thread
+            errors.append(e)
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join(60)
+    if errors:
+        raise errors[0]
+    torch.cuda.synchronize()
+    for i in range(2):
+        assert len(got[i]) == 40
+        for o, lists in got[i]:
+            assert (o.cpu().numpy() == cases[i][1]).all()
+            _same(lists, cases[i][3])
